@@ -27,14 +27,11 @@
 #include <stdexcept>
 #include <type_traits>
 
+#include "conv_dev.hpp"
 #include "kernels.hpp"
 
 namespace dycl {
 namespace k {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct ConvP {
   const uint16_t* src;
@@ -75,42 +72,6 @@ struct ConvP {
   float* gap;              // conv_lds_kernel: 32-row chunk column sums of the bf16 output, or null
   int rev;                 // conv_lds_kernel: each XCD walks its tiles last to first
 };
-
-// round to nearest even (v_cvt_pk_bf16_f32; NaN stays NaN), as every
-// kernel's epilogue
-__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f)); }
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const bf16x2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
-  return __builtin_bit_cast(uint32_t, v);
-}
-
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
-
-// the element row (image * HoWo + pixel) that layer row `row` maps to
-// through an image list (null: itself)
-__device__ __forceinline__ size_t row_at(const int32_t* rows, int row, int HoWo) {
-  if (!rows) return static_cast<size_t>(row);
-  const int img = row / HoWo;
-  return static_cast<size_t>(rows[img]) * HoWo + (row - img * HoWo);
-}
-
-template <int ACT>
-__device__ __forceinline__ float act_t(float v) {
-  if (ACT == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (ACT == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
-  if (ACT == ACT_TANH) return tanhf(v);
-  return v;
-}
-
-__device__ __forceinline__ float apply_act(float v, int act) {
-  if (act == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (act == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
-  if (act == ACT_TANH) return tanhf(v);
-  return v;
-}
-
-__device__ __forceinline__ float sigmoidf(float v) { return 1.0f / (1.0f + expf(-v)); }
 
 template <int BM, int BN, int WM, int WN, int KS, bool SCALAR, int BK = 64, int STAGES = 1>
 __global__ __launch_bounds__(64 * WM* WN) void conv_kernel(ConvP p) {
@@ -332,18 +293,6 @@ __global__ __launch_bounds__(64 * WM* WN) void conv_kernel(ConvP p) {
 // global chunk that belongs at its fixed LDS slot.  Padding taps and rows
 // past M read a zero buffer.  Two LDS stages, one barrier per K step: the
 // loads of step k+1 are in flight while step k's MFMAs run.
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-
-// Wait until at most N vector-memory operations of this thread are still in
-// flight (loads complete in order, so every older one - the tile about to be
-// read - has landed), then barrier.  Inline asm with a memory clobber keeps
-// the compiler from moving LDS reads across it and from widening the wait.
-template <int N>
-__device__ __forceinline__ void wait_vm_barrier() {
-  static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
 // One K step (NS 1) is the memory-bound 1x1 case, whose speed follows the
 // number of workgroups in flight: its registers are capped for five waves
 // per SIMD (128 x 64 tiles: 85 VGPRs, the accumulators out of AGPRs, no
@@ -721,23 +670,6 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
     epilogue(std::integral_constant<int, ACT_NONE>{});
 }
 
-// 16 bytes per lane from a raw buffer straight into LDS at `lds` + 16 * lane:
-// the buffer spans `bytes` from `base`, and a load at or past its end (an
-// offset of 2^31 or more included) writes zeros instead of reading memory.
-__device__ __forceinline__ void buffer_load_lds16(const void* base, uint32_t bytes, uint32_t offset, lds_void_ptr lds) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, offset, 0, 0, 0);
-}
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// 16 bytes per lane to a raw buffer of `bytes` from `base`; a store at or
-// past its end is dropped.
-__device__ __forceinline__ void buffer_store16(void* base, uint32_t bytes, uint32_t offset, u32x4 v) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, offset, 0, 0);
-}
-
 // --------------------------------- 3x3 conv, halo tiles, resident weights ----
 // For 3x3 / stride 1 / pad 1 layers with 64 input and 64 output channels,
 // and for stems with 8 (padded) input channels and 64 output channels.
@@ -789,14 +721,11 @@ struct Conv3P {
   const int32_t* drows;
 };
 
-constexpr int kW3Patch = 256;                      // patch pixels per buffer (= kHP)
+constexpr int kW3Patch = 256;                      // patch pixels per buffer
 constexpr int kW3RB = 128 * 128;                   // 16384 B: a tile of residual / output rows
 // patch bytes per pixel and per buffer, by input channels
 constexpr int w3_pxb(int cin) { return cin == 8 ? 16 : 144; }
 constexpr int w3_pb(int cin) { return kW3Patch * w3_pxb(cin); }
-
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-__device__ __forceinline__ void all_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int CIN, int ACT, bool RES>
 __global__ __launch_bounds__(512) void conv3_wres_kernel(Conv3P p) {
@@ -1083,356 +1012,6 @@ __global__ __launch_bounds__(512) void conv3_wres_kernel(Conv3P p) {
   }
 }
 
-// ------------------------------ 3x3 conv, halo tiles, streamed weights ----
-// For 3x3 / stride 1 / pad 1 layers with Cin and Cout multiples of 64.  A
-// persistent workgroup walks a contiguous range of work units, a unit being
-// one BM-pixel output tile (128 as launched; the row / image geometry of the
-// kernel above) times BN output channels.  The K loop runs over 64-channel chunks and,
-// inside a chunk, the nine taps: one step = one tap of one chunk = 64 of K.
-//  * the input patch of a chunk (the tile's pixels plus the one-pixel halo,
-//    144 bytes per pixel) is staged in LDS once and read by all nine taps;
-//    it is double-buffered, and the next chunk's patch is requested at the
-//    first step of the current chunk, nine steps before it is needed;
-//  * the weights of a step (BN rows x 128 bytes, XOR-swizzled) stream
-//    through NS LDS stages, NS - 1 steps ahead of the MFMAs.
-// Eight waves, one barrier per step: four compute waves (2 x 2, each
-// BM/2 pixels x BN/2 channels: 4 or 2 MFMA blocks of 32 pixels by BN/64
-// blocks of 32 channels) touch global memory only in the epilogue;
-// two weight loader waves and two patch loader waves issue every load
-// straight into LDS.  Each loader role waits only for its own loads (the memory counter
-// completes in order, so one role's slow loads never hold up the other's):
-// the weight loaders for step g's weights, issued NS - 1 steps earlier; the
-// patch loaders, at a chunk start, for that chunk's patch.
-//
-// MFMA operands: A = weights (32 output channels), B = patch pixels, so a
-// lane's results are 4 consecutive channels of one pixel per group and the
-// epilogue writes 8-byte pieces of NHWC rows directly; scale and shift of
-// every output channel are kept in LDS.
-struct Conv3HP {
-  const uint16_t* src;
-  const uint16_t* w;       // [cout_pad][Kp] packed, K = tap * cin + ci
-  const float* scale;
-  const float* shift;
-  const uint16_t* res;
-  uint16_t* dst;
-  const uint16_t* zeros;
-  int n, H, W, cin, cout, Kp;
-  int RS, segs, PW, NP, tpi;
-  int ntiles, units, nch;  // output channel tiles, units, 64-channel chunks
-  const int32_t* nc;       // device count of live images (<= n) or null
-};
-
-constexpr int kHP = 256;                           // patch pixels per buffer of 128-pixel tiles
-constexpr int kHMaxC = 512;                        // output channels whose scale / shift fit LDS
-// patch loads per patch-loader thread and chunk (128 threads x 16 bytes),
-// and patch capacity in pixels, by tile height
-constexpr int halo_jp(int bm) { return bm == 128 ? 18 : 24; }
-constexpr int halo_cap(int bm) { return halo_jp(bm) * 128 / 9; }
-
-template <int BM, int BN, int WA, int ACT, bool RES, int kHNS>
-__global__ __launch_bounds__(64 * (BM / (16 * WA) + 4)) void conv3h_kernel(Conv3HP p) {
-  constexpr int CW = BM / (16 * WA);               // compute waves (BM / (32 WA) x 2)
-  constexpr int JW = BN / 16;                      // weight loads per weight-loader thread and step
-  constexpr int JP = halo_jp(BM);                  // patch loads per patch-loader thread and chunk
-  constexpr int kHPB = JP * 128 * 16;              // patch buffer bytes
-  constexpr int WSTAGE = BN * 128;
-  constexpr int TB = BN / 64;                      // 32-channel blocks per compute wave
-  static_assert(kHNS >= 3 && (kHNS - 3) * JW < 64, "stage count");
-  __shared__ __align__(16) char smem[kHNS * WSTAGE + 2 * kHPB + 2 * kHMaxC * 4];
-  char* const wbuf = smem;
-  char* const pbuf = smem + kHNS * WSTAGE;
-  float* const ssl = reinterpret_cast<float*>(pbuf + 2 * kHPB);   // [scale | shift]
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wv = __builtin_amdgcn_readfirstlane(wave);   // the same, known wave-uniform
-  const int HW = p.H * p.W;
-  const int n = p.nc ? min(*p.nc, p.n) : p.n;
-  const int units = p.nc ? (p.tpi ? n * p.tpi : (n + p.segs - 1) / p.segs) * p.ntiles : p.units;
-  const int u_begin = static_cast<int>((static_cast<long>(units) * blockIdx.x) / gridDim.x);
-  const int u_end = static_cast<int>((static_cast<long>(units) * (blockIdx.x + 1)) / gridDim.x);
-  if (u_begin >= u_end) return;
-  const int S = 9 * p.nch;                         // steps per unit
-  const int T = (u_end - u_begin) * S;             // steps of this workgroup
-
-  // unit -> (pixel tile, channel tile); consecutive units share the pixel tile
-  auto unit_geom = [&](int u, int& img, int& oh0, int& m0, int& lim, int& n0) __attribute__((always_inline)) {
-    const int mt = u / p.ntiles;
-    n0 = (u - mt * p.ntiles) * BN;
-    if (p.tpi) {
-      img = mt / p.tpi;
-      oh0 = (mt - img * p.tpi) * p.RS;
-      m0 = img * HW + oh0 * p.W;
-      lim = min(p.RS, p.H - oh0) * p.W;
-    } else {
-      img = mt * p.segs;
-      oh0 = 0;
-      m0 = img * HW;
-      lim = min(p.segs, n - img) * HW;
-    }
-  };
-
-  if (wv >= CW + 2) {
-    // ---------------- patch loader waves ----------------
-    // Buffer loads straight into LDS.  A chunk's loads use one buffer
-    // resource spanning the tile's image(s) from the chunk's first channel;
-    // a load outside it returns zeros, which is the convolution's padding:
-    // a slot's byte offset is taken relative to the tile's first output row
-    // (row mode: plus oh0 rows, so the halo row above image row 0 wraps to
-    // a huge offset, and rows past the image exceed the resource), and slots
-    // that can never hold data (zero columns, the unused ninth slot, past
-    // the patch, the halo rows of image mode) get an offset above 2^31.
-    const int lt = tid - (CW + 2) * 64, lw = wv - (CW + 2);
-    const int rowb = p.W * p.cin * 2, imgb = p.H * rowb;
-    uint32_t vofs[JP];
-#pragma unroll
-    for (int i = 0; i < JP; ++i) {
-      const int u = i * 128 + lt, q = u / 9, ch = u - (u / 9) * 9;
-      const int segpix = (p.RS + 2) * p.PW;
-      const int sg = q / segpix, rem = q - sg * segpix;
-      const int pr = rem / p.PW, pc = rem - (rem / p.PW) * p.PW;
-      bool data = q < p.NP && ch < 8 && pc >= 1 && pc <= p.W;
-      if (!p.tpi) data = data && pr >= 1 && pr <= p.H;
-      vofs[i] = data ? static_cast<uint32_t>(sg * imgb + (pr - 1) * rowb + (pc - 1) * p.cin * 2 + ch * 16) : 0xC0000000u;
-    }
-    // chunk iterator: (unit, chunk) of the next patch to request
-    int pu = u_begin, pc_ = 0;
-    const uint16_t* rbase = p.src;                 // the chunk's buffer: base and size
-    uint32_t rbytes = 0;
-    uint32_t tofs = 0;                             // row mode: oh0 rows, in bytes
-    auto set_chunk = [&]() __attribute__((always_inline)) {
-      int img = 0, oh0 = 0, nimg = 0;
-      if (pu < u_end) {
-        int m0, lim, n0;
-        unit_geom(pu, img, oh0, m0, lim, n0);
-        nimg = p.tpi ? 1 : min(p.segs, n - img);
-      }
-      rbase = p.src + (size_t)img * p.H * p.W * p.cin + pc_ * 64;
-      rbytes = nimg ? nimg * imgb - pc_ * 128 : 0;
-      tofs = static_cast<uint32_t>(oh0) * rowb;
-    };
-    set_chunk();
-    // loads k0 .. k1-1 of the patch of chunk sequence number cs
-    auto issue_patch = [&](int cs, int k0, int k1) __attribute__((always_inline)) {
-      char* pb = pbuf + (cs & 1) * kHPB;
-#pragma unroll
-      for (int i = 0; i < JP; ++i) {
-        if (i < k0 || i >= k1) continue;
-        buffer_load_lds16(rbase, rbytes, vofs[i] + tofs, (lds_void_ptr)(pb + (i * 128 + lw * 64) * 16));
-      }
-    };
-    auto next_chunk = [&]() __attribute__((always_inline)) {
-      if (++pc_ == p.nch) {
-        pc_ = 0;
-        ++pu;
-      }
-      set_chunk();
-    };
-    issue_patch(0, 0, JP);
-    next_chunk();
-    // chunk q + 1 is requested in six pieces over the first six steps of
-    // chunk q and must have landed before the barrier of step 9q + 8 (whose
-    // compute waves prefetch the first operands of step 9(q + 1)).
-    // Iteration k precedes the barrier that starts compute step k, k = 0..T.
-    int r = 0;
-    for (int k = 0; k <= T; ++k) {
-      if (k == 0 || r == 8)
-        wait_vm_barrier<0>();
-      else
-        asm volatile("s_barrier" ::: "memory");
-      if (r < 6) {
-        const int cs = k / 9 + 1;
-        if (r == 0) issue_patch(cs, 0, JP / 6);
-        else if (r == 1) issue_patch(cs, JP / 6, 2 * JP / 6);
-        else if (r == 2) issue_patch(cs, 2 * JP / 6, 3 * JP / 6);
-        else if (r == 3) issue_patch(cs, 3 * JP / 6, 4 * JP / 6);
-        else if (r == 4) issue_patch(cs, 4 * JP / 6, 5 * JP / 6);
-        else {
-          issue_patch(cs, 5 * JP / 6, JP);
-          next_chunk();
-        }
-      }
-      if (++r == 9) r = 0;
-    }
-    wait_vm_barrier<0>();                          // the last (placeholder) chunk, before the workgroup ends
-    return;
-  }
-
-  if (wv >= CW) {
-    // ---------------- weight loader waves ----------------
-    // one buffer resource per step (its weights: BN rows from the step's K
-    // offset); each thread's slots are constant byte offsets from it
-    const int lt = tid - CW * 64, lw = wv - CW;
-    uint32_t wofs[JW];
-#pragma unroll
-    for (int k = 0; k < JW; ++k) {
-      const int u = k * 128 + lt, row = u >> 3, pos = u & 7;
-      wofs[k] = static_cast<uint32_t>(row * p.Kp + ((pos ^ ((row >> 1) & 7)) * 8)) * 2;
-    }
-    const uint32_t wbytes = static_cast<uint32_t>(p.ntiles * BN) * p.Kp * 2;
-    // step iterator of the next weights to request: unit, its channel
-    // tile, chunk and tap (K offset tap * cin + chunk * 64)
-    int wu = u_begin, wnt = u_begin % p.ntiles, wc = 0, wt = 0, ws_i = 0;
-    auto issue_weights = [&]() __attribute__((always_inline)) {
-      const uint32_t e0 = static_cast<uint32_t>(wnt * BN) * p.Kp + wt * p.cin + wc * 64;
-      const uint32_t wb = wu < u_end ? wbytes - e0 * 2 : 0;
-      char* ws = wbuf + ws_i * WSTAGE;
-#pragma unroll
-      for (int k = 0; k < JW; ++k)
-        buffer_load_lds16(p.w + e0, wb, wofs[k], (lds_void_ptr)(ws + (k * 128 + lw * 64) * 16));
-      if (++ws_i == kHNS) ws_i = 0;
-      if (++wt == 9) {
-        wt = 0;
-        if (++wc == p.nch) {
-          wc = 0;
-          ++wu;
-          if (++wnt == p.ntiles) wnt = 0;
-        }
-      }
-    };
-    for (int k = 0; k < kHNS - 1; ++k) issue_weights();
-    // iteration k precedes the barrier that starts compute step k: steps k
-    // and k + 1 must be resident (step k + 1's first operands are read
-    // during step k), i.e. everything up to step k + 1's weights, issued
-    // NS - 2 iterations ago
-    for (int k = 0; k <= T; ++k) {
-      wait_vm_barrier<(kHNS - 3) * JW>();
-      issue_weights();                             // step k + NS - 1, into the stage of step k - 1
-    }
-    wait_vm_barrier<0>();
-    return;
-  }
-
-  // ---------------- compute waves ----------------
-  for (int c = tid; c < p.cout; c += CW * 64) {
-    ssl[c] = p.scale ? p.scale[c] : 1.0f;
-    ssl[kHMaxC + c] = p.shift ? p.shift[c] : 0.0f;
-  }
-  const int wm = wave >> 1, wn = wave & 1, hi = lane >> 5;
-  int pix0[WA];
-#pragma unroll
-  for (int a = 0; a < WA; ++a) {
-    const int i = wm * (32 * WA) + a * 32 + (lane & 31);
-    const int sg = i / (p.RS * p.W), r = (i / p.W) - sg * p.RS, c = i - (i / p.W) * p.W;
-    pix0[a] = sg < p.segs ? (sg * (p.RS + 2) + r) * p.PW + c : 0;
-  }
-  int wrow[TB];
-#pragma unroll
-  for (int b = 0; b < TB; ++b) wrow[b] = wn * (BN / 2) + b * 32 + (lane & 31);
-
-  f32x16 acc[TB][WA];
-#pragma unroll
-  for (int b = 0; b < TB; ++b)
-#pragma unroll
-    for (int a = 0; a < WA; ++a)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[b][a][r] = 0.f;
-
-  // fragment addresses of a step: weight stage and patch window
-  auto step_ptrs = [&](int st_, int pbi_, int tap_, const char*& ws_, const char*& pb_) __attribute__((always_inline)) {
-    const int dy = tap_ / 3, dx = tap_ - (tap_ / 3) * 3;
-    ws_ = wbuf + st_ * WSTAGE;
-    pb_ = pbuf + pbi_ * kHPB + (dy * p.PW + dx) * 144 + hi * 16;
-  };
-  bf16x8 wf[2][TB], pf[2][WA];
-  auto fetch = [&](const char* ws_, const char* pb_, int s, int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int b = 0; b < TB; ++b)
-      wf[slot][b] = *reinterpret_cast<const bf16x8*>(ws_ + wrow[b] * 128 + (((2 * s + hi) ^ ((wrow[b] >> 1) & 7)) << 4));
-#pragma unroll
-    for (int a = 0; a < WA; ++a) pf[slot][a] = *reinterpret_cast<const bf16x8*>(pb_ + pix0[a] * 144 + s * 32);
-  };
-  int tap = 0, jc = 0, cu = u_begin, st = 0, pbi = 0;   // tap, step in unit, unit, stage, patch buffer
-  // the barrier of step g also guarantees step g + 1's data, so the first
-  // operands of step g + 1 are read before it
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // scale / shift; steps 0 and 1
-  const char* ws;
-  const char* pb;
-  step_ptrs(0, 0, 0, ws, pb);
-  fetch(ws, pb, 0, 0);
-  for (int g = 0; g < T; ++g) {
-    const bool unit_end = jc == S - 1;
-    // the next step's stage / patch buffer / tap
-    int st1 = st + 1 == kHNS ? 0 : st + 1, tap1 = tap + 1, pbi1 = pbi;
-    if (tap1 == 9) {
-      tap1 = 0;
-      pbi1 ^= 1;
-    }
-    const char* ws1;
-    const char* pb1;
-    step_ptrs(st1, pbi1, tap1, ws1, pb1);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s + 1 < 4)
-        fetch(ws, pb, s + 1, (s + 1) & 1);
-      else if (g + 1 < T)
-        fetch(ws1, pb1, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int a = 0; a < WA; ++a)
-          acc[b][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s & 1][b], pf[s & 1][a], acc[b][a], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    st = st1;
-    tap = tap1;
-    pbi = pbi1;
-    ws = ws1;
-    pb = pb1;
-    if (++jc == S) jc = 0;
-
-    if (unit_end) {
-      // unit done: epilogue straight to global memory, 8 bytes per group
-      int img, oh0, m0, lim, n0;
-      unit_geom(cu++, img, oh0, m0, lim, n0);
-#pragma unroll
-      for (int a = 0; a < WA; ++a) {
-        const int px = wm * (32 * WA) + a * 32 + (lane & 31);
-        const bool live = px < lim;
-        const size_t rowo = (size_t)(m0 + (live ? px : 0)) * p.cout;
-        uint2 rr[TB][4];
-        if (RES && live) {
-#pragma unroll
-          for (int b = 0; b < TB; ++b)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              rr[b][q] = *reinterpret_cast<const uint2*>(p.res + rowo + n0 + wn * (BN / 2) + b * 32 + 8 * q + 4 * hi);
-        }
-#pragma unroll
-        for (int b = 0; b < TB; ++b)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int c0 = n0 + wn * (BN / 2) + b * 32 + 8 * q + 4 * hi;
-            const float4 sc = *reinterpret_cast<const float4*>(ssl + c0);
-            const float4 sh = *reinterpret_cast<const float4*>(ssl + kHMaxC + c0);
-            float v[4] = {fmaf(acc[b][a][4 * q], sc.x, sh.x), fmaf(acc[b][a][4 * q + 1], sc.y, sh.y),
-                          fmaf(acc[b][a][4 * q + 2], sc.z, sh.z), fmaf(acc[b][a][4 * q + 3], sc.w, sh.w)};
-            if (RES) {
-              v[0] += __uint_as_float(rr[b][q].x << 16);
-              v[1] += __uint_as_float(rr[b][q].x & 0xffff0000u);
-              v[2] += __uint_as_float(rr[b][q].y << 16);
-              v[3] += __uint_as_float(rr[b][q].y & 0xffff0000u);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = apply_act(v[e], ACT);
-            bf16x2 lo = {(__bf16)v[0], (__bf16)v[1]}, hv = {(__bf16)v[2], (__bf16)v[3]};
-            if (live)
-              *reinterpret_cast<uint2*>(p.dst + rowo + c0) =
-                  make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hv));
-          }
-      }
-#pragma unroll
-      for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int a = 0; a < WA; ++a)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[b][a][r] = 0.f;
-    }
-    // this step's LDS reads are done; step g + 2's data is ready after it
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  }
-}
-
 // ------------------------------------------------------- K-split sums ----
 // y[m, c..c+7] = finish(sum_s part[s][m][c..c+7]) with the splits added in
 // order s = 0, 1, ...: scale / shift, residual, activation, bf16 rounding,
@@ -1632,7 +1211,7 @@ bool conv3_wres(const ConvArgs& a, hipStream_t s) {
   const bool stem = a.cin == 8 && a.Kp == 128 && a.k == 3 && a.stride == 1 && a.pad == 1 && !a.src2 && !a.out_f32 &&
                     a.Ho == a.H && a.Wo == a.W &&
                     !((reinterpret_cast<uintptr_t>(a.scale) | reinterpret_cast<uintptr_t>(a.shift)) & 15);
-  if (!(stem || (is_halo_layer(a) && a.cin == 64)) || a.cout != 64 || !halo_geom(a.n, a.H, a.W, 128, kHP, g))
+  if (!(stem || (is_halo_layer(a) && a.cin == 64)) || a.cout != 64 || !halo_geom(a.n, a.H, a.W, 128, kW3Patch, g))
     return false;
   const int cus = cu_count();
   if (!cus) return false;
@@ -1683,73 +1262,6 @@ bool conv3_wres(const ConvArgs& a, hipStream_t s) {
     DYCL_W(64)
   }
 #undef DYCL_W
-  return true;
-}
-
-// the streamed-weights 3x3 kernel (Cin, Cout multiples of 64) on 128-pixel
-// tiles: measured 2-5 % faster than 256-pixel tiles on the ResNet-50
-// stage-2 / 3 and ResNet-18 stage-2 layers (interleaved runs, best of four
-// each), and a shape whose 128-pixel patch does not fit LDS fits no
-// 256-pixel patch either, once the smallest images (taken by the implicit
-// GEMM, below) are set aside
-bool conv3_halo(const ConvArgs& a, hipStream_t s) {
-  if (!is_halo_layer(a) || a.cout > kHMaxC) return false;
-  // images so small that the halo more than doubles the patch (4 x 4: 36
-  // pixels for 16) go to the implicit GEMM, which is faster there
-  if (a.H * a.W <= 128 && 2 * a.H * a.W < (a.H + 2) * (a.W + 2)) return false;
-  const int cus = cu_count();
-  if (!cus) return false;
-  // the tile shape follows the expected live images; the geometry (and the
-  // grid) is then laid out for all n
-  const int nh = a.nhint > 0 && a.nhint < a.n ? a.nhint : a.n;
-  HaloGeom g;
-  constexpr int bm = 128;
-  if (!halo_geom(nh, a.H, a.W, bm, halo_cap(bm), g)) return false;
-  const int bn = (a.cout % 128 == 0 && conv_cout_pad(a.cout) % 128 == 0 && (long)g.mtiles * (a.cout / 128) >= cus)
-                     ? 128 : 64;
-  if (!halo_geom(a.n, a.H, a.W, bm, halo_cap(bm), g)) return false;
-  Conv3HP p;
-  p.src = a.src;
-  p.w = a.w;
-  p.scale = a.scale;
-  p.shift = a.shift;
-  p.res = a.res;
-  p.dst = static_cast<uint16_t*>(a.dst);
-  p.zeros = a.zeros;
-  p.n = a.n;
-  p.H = a.H;
-  p.W = a.W;
-  p.cin = a.cin;
-  p.cout = a.cout;
-  p.Kp = a.Kp;
-  p.RS = g.RS;
-  p.segs = g.segs;
-  p.tpi = g.tpi;
-  p.PW = g.PW;
-  p.NP = g.NP;
-  p.ntiles = a.cout / bn;
-  p.units = g.mtiles * p.ntiles;
-  p.nch = a.cin / 64;
-  p.nc = a.ncount;
-  const int grid = p.units < cus ? p.units : cus;
-  // four compute waves of 64 x BN/2 (pixels x channels), four loader waves
-  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, s, p); };
-#define DYCL_H(BM, BN, NS)                                                              \
-  if (p.res) {                                                                          \
-    if (a.act == ACT_RELU) go(conv3h_kernel<BM, BN, BM / 64, ACT_RELU, true, NS>);      \
-    else if (a.act == ACT_GELU) go(conv3h_kernel<BM, BN, BM / 64, ACT_GELU, true, NS>); \
-    else go(conv3h_kernel<BM, BN, BM / 64, ACT_NONE, true, NS>);                        \
-  } else {                                                                              \
-    if (a.act == ACT_RELU) go(conv3h_kernel<BM, BN, BM / 64, ACT_RELU, false, NS>);     \
-    else if (a.act == ACT_GELU) go(conv3h_kernel<BM, BN, BM / 64, ACT_GELU, false, NS>); \
-    else go(conv3h_kernel<BM, BN, BM / 64, ACT_NONE, false, NS>);                       \
-  }
-  if (bn == 128) {
-    DYCL_H(128, 128, 5)
-  } else {
-    DYCL_H(128, 64, 8)
-  }
-#undef DYCL_H
   return true;
 }
 
@@ -1876,7 +1388,7 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
   // (image mode) or the implicit GEMM
   const bool listed = a.src_rows || a.src2_rows || a.res_rows || a.dst_rows;
   if (conv3_narrow(a, s)) return false;   // 16 / 32 channels: row lists allowed
-  if (vec_out && (listed ? conv3_wres(a, s) : (conv3_wres(a, s) || conv3_halo(a, s)))) return false;
+  if (vec_out && (listed ? conv3_wres(a, s) : (conv3_wres(a, s) || conv3_tiles(a, s)))) return false;
   if (vec_out) {
     // deep K on few pixels per image: K ranges of one tile on several
     // workgroups, fp32 partials summed in a fixed order by a second kernel
@@ -1946,6 +1458,7 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
     dispatch_staged<3>(c, p, s);
   else
     dispatch_staged<7>(c, p, s);
+  return false;
 }
 
 }  // namespace k

@@ -160,6 +160,11 @@ bool conv_rgb_stem(const ConvArgs& a, hipStream_t s);
 // other arguments.
 bool conv3_narrow(const ConvArgs& a, hipStream_t s);
 
+// 3x3 / stride-1 / pad-1 layers with Cin and Cout multiples of 64 on images
+// of 5 x 5 and larger (no row lists; device counts allowed): a halo kernel on
+// linear pixel tiles.  Returns false (launching nothing) for other arguments.
+bool conv3_tiles(const ConvArgs& a, hipStream_t s);
+
 // K ranges per output tile for the layer shape (1: none).  A split layer
 // needs conv_ksplit_bytes of workspace; without it the layer runs unsplit
 // (the same sums in another order).  Depends on the shape only, so every

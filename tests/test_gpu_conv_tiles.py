@@ -1,0 +1,36 @@
+"""The 3x3 kernel on linear pixel tiles (stride 1, Cin and Cout multiples of
+64) through dycl_op_conv, at the geometries where its tiles can go wrong:
+tiles that cross rows and images, a ragged last tile, images of two pixels'
+width, of two rows, and as wide as the patch allows, several input chunks,
+and each of its three tile sizes; against the oracle's convolution with the
+bound of test_gpu_conv (fp32 accumulation, one rounding to bf16)."""
+
+import pytest
+
+from tests.test_gpu_conv import _case
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # n, H, W, cin, cout, k, stride, pad, residual, act
+    (201, 12, 12, 64, 128, 3, 1, 1, False, 1),   # 128 x 128 tiles: every tile crosses rows, most an image
+    (31, 28, 29, 64, 128, 3, 1, 1, True, 1),     # odd width, ragged last tile
+    (127, 14, 14, 128, 128, 3, 1, 1, True, 2),   # two input chunks, GELU
+    (100, 5, 5, 64, 1024, 3, 1, 1, False, 0),    # five images per tile, eight channel tiles
+    (9, 56, 56, 64, 128, 3, 1, 1, True, 1),      # 128 x 64 tiles: wide images
+    (3, 6, 79, 64, 128, 3, 1, 1, False, 1),      # the widest image a tile's patch holds
+    (170, 14, 14, 128, 64, 3, 1, 1, False, 1),   # 64 output channels
+    (1, 5, 5, 64, 128, 3, 1, 1, True, 1),        # 64 x 64 tiles: one tile, 25 of 64 pixels
+    (3, 3, 43, 64, 128, 3, 1, 1, False, 1),
+    (5, 2, 65, 64, 64, 3, 1, 1, False, 1),       # (64 -> 64 keeps the register-weight kernel)
+    (5, 2, 65, 128, 64, 3, 1, 1, False, 1),      # two rows per image
+    (4, 70, 2, 64, 128, 3, 1, 1, True, 1),       # two pixels per row
+    (13, 7, 7, 256, 128, 3, 1, 1, True, 0),      # four input chunks
+    (2, 3, 80, 64, 128, 3, 1, 1, False, 1),      # one pixel too wide: the implicit GEMM
+    (300, 1, 1, 64, 128, 3, 1, 1, False, 1),     # 1 x 1 images: the implicit GEMM
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "n{}_{}x{}_{}to{}".format(*c[:5]))
+def test_conv3_tiles(case):
+    _case(*case, seed=hash(case) % (2 ** 31))
