@@ -33,6 +33,7 @@
 #include <string>
 
 #include "halt_row.hpp"
+#include "gelu.hpp"
 #include "kernels.hpp"
 
 namespace dycl {
@@ -84,7 +85,7 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-__device__ __forceinline__ float gelu(float v) { return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f)); }
+__device__ __forceinline__ float gelu(float v) { return gelu_f32(v); }
 
 __global__ __launch_bounds__(kNT) void act_loop_kernel(ActLoopP p) {
   __shared__ __align__(16) char smem[kNS * kStage];

@@ -20,6 +20,7 @@
 // Persistent: the next unit's input rows are loaded into registers while the
 // current one computes.  Images are addressed through the row lists (fused
 // gate gathers / scatters) and the live count of the device host modes.
+#include "gelu.hpp"
 #include "kernels.hpp"
 
 namespace dycl {
@@ -71,7 +72,7 @@ struct NarrowP {
 template <int ACT>
 __device__ __forceinline__ float narrow_act(float v) {
   if (ACT == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (ACT == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  if (ACT == ACT_GELU) return gelu_f32(v);
   return v;
 }
 

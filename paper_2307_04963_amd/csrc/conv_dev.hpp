@@ -2,6 +2,7 @@
 // epilogues' arithmetic, loads straight into LDS and barriers.
 #pragma once
 
+#include "gelu.hpp"
 #include "kernels.hpp"
 
 namespace dycl {
@@ -35,14 +36,14 @@ __device__ __forceinline__ size_t row_at(const int32_t* rows, int row, int HoWo)
 template <int ACT>
 __device__ __forceinline__ float act_t(float v) {
   if (ACT == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (ACT == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  if (ACT == ACT_GELU) return gelu_f32(v);
   if (ACT == ACT_TANH) return tanhf(v);
   return v;
 }
 
 __device__ __forceinline__ float apply_act(float v, int act) {
   if (act == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (act == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  if (act == ACT_GELU) return gelu_f32(v);
   if (act == ACT_TANH) return tanhf(v);
   return v;
 }
@@ -67,12 +68,23 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, uint32_t byt
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds, 16, offset, 0, 0, 0);
 }
 
+// 16 bytes per lane from a raw buffer of `bytes` from `base`; zeros at or past its end
+__device__ __forceinline__ u32x4 buffer_load16(const void* base, uint32_t bytes, uint32_t offset) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+  return __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, 0);
+}
+
 // 16 bytes per lane to a raw buffer of `bytes` from `base`; a store at or
 // past its end is dropped.
 __device__ __forceinline__ void buffer_store16(void* base, uint32_t bytes, uint32_t offset, u32x4 v) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
   __builtin_amdgcn_raw_buffer_store_b128(v, r, offset, 0, 0);
 }
+
+// (M0, which the loads below set, is a reserved register: the compiler is told
+// of the write and keeps nothing there, which is all the warning is about)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 
 // 16 bytes per lane from `src` (per lane) straight into LDS at `lds` + 16 *
 // lane (the same for all lanes).  Unlike the builtin the compiler does not
@@ -85,6 +97,33 @@ __device__ __forceinline__ void load_lds16(const void* src, const void* lds) {
                :
                : "s"((lds_void_ptr)(lds)), "v"(src)
                : "memory", "m0");
+}
+
+// the same from `base` (the same for all lanes) + a byte offset per lane
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t offset, const void* lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"((lds_void_ptr)(lds)), "v"(offset), "s"(base)
+               : "memory", "m0");
+}
+
+// the same from a raw buffer: `offset` (per lane) past its end brings zeros;
+// `add` (the same for all lanes) moves the address within it
+__device__ __forceinline__ void buffer_lds16(u32x4 rsrc, uint32_t offset, uint32_t add, const void* lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"((lds_void_ptr)(lds)), "v"(offset), "s"(rsrc), "s"(add)
+               : "memory", "m0");
+}
+
+#pragma clang diagnostic pop
+
+// a raw buffer's descriptor, in scalar registers
+__device__ __forceinline__ u32x4 raw_buffer(const void* base, uint32_t bytes) {
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  return u32x4{static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b))),
+               static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32) & 0xffffu)),
+               static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(bytes)), 0x00020000u};
 }
 
 // every load and LDS access of this thread done, then barrier; waits that the

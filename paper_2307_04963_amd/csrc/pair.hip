@@ -33,6 +33,7 @@
 // LDS 74.5 KB: two workgroups per CU.
 #include <stdexcept>
 
+#include "gelu.hpp"
 #include "kernels.hpp"
 
 namespace dycl {
@@ -71,7 +72,7 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
 template <int ACT>
 __device__ __forceinline__ float act_of(float v) {
   if (ACT == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (ACT == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  if (ACT == ACT_GELU) return gelu_f32(v);
   return v;
 }
 

@@ -29,6 +29,7 @@
 // Measured on the ResNet-50 stem at batch 256 (224 x 224 -> 112 x 112): the
 // epilogue (conversion and 411 MB of stores) takes about half the time, the
 // MFMA loop and the staging of the input rows the other half.
+#include "gelu.hpp"
 #include "kernels.hpp"
 
 namespace dycl {
@@ -95,7 +96,7 @@ __device__ __forceinline__ u32x4 max_bf16x8(u32x4 a, u32x4 b) {
 template <int ACT>
 __device__ __forceinline__ float act_of(float v) {
   if (ACT == ACT_RELU) return v > 0.f ? v : 0.f;
-  if (ACT == ACT_GELU) return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
+  if (ACT == ACT_GELU) return gelu_f32(v);
   return v;
 }
 
