@@ -48,6 +48,7 @@ struct ConvP {
   const int32_t* srows;
   const int32_t* s2rows;   // image list of src2 (the concatenated input)
   int H2, W2, s2;          // src2: spatial shape and the stride it is read at
+  uint32_t src_bytes;      // conv_lds_kernel with scalar taps: size of src
   const int32_t* rrows;
   const int32_t* drows;
   // a folded projection (conv_lds_kernel, no K split): its kfold K steps
@@ -291,15 +292,17 @@ __global__ __launch_bounds__(64 * WM* WN) void conv_kernel(ConvP p) {
 // every ds_read_b128 phase of the MFMA operand reads hit 16 distinct bank
 // groups.  The swizzle is applied on the global side: each lane picks the
 // global chunk that belongs at its fixed LDS slot.  Padding taps and rows
-// past M read a zero buffer.  Two LDS stages, one barrier per K step: the
-// loads of step k+1 are in flight while step k's MFMAs run.
-// One K step (NS 1) is the memory-bound 1x1 case, whose speed follows the
+// past M read a zero buffer.  With NS LDS stages the loads of step k + NS - 1
+// are issued between the MFMAs of step k, as are the LDS reads of the next
+// sub-step's operands (left to itself the compiler reads an operand, waits
+// and runs its one or two MFMAs, and puts a wait for every load in flight
+// before each LDS read), with one barrier per step.
+// NS 1 is the memory-bound case of few K steps, whose speed follows the
 // number of workgroups in flight: its registers are capped for five waves
-// per SIMD (128 x 64 tiles: 85 VGPRs, the accumulators out of AGPRs, no
-// spill), where unconstrained it takes 85 + 32 AGPRs and runs four; a cap
-// for six spills.
-template <int BM, int BN, int WM, int WN, int KS, int NS = 2>
-__global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS == 1 ? 5 : 1))) void conv_lds_kernel(
+// per SIMD (four with 128 x 128 and 128 x 256 tiles; one spilled register per
+// lane cost 20 %).
+template <int BM, int BN, int WM, int WN, int KS, int NS, bool LEAN, bool UNI>
+__global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS == 1 ? (BN >= 128 ? 4 : 5) : 2))) void conv_lds_kernel(
     ConvP p) {
   constexpr int NT = 64 * WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -309,7 +312,7 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
   constexpr int EPW = WTN + 4;                        // epilogue row stride (floats)
   constexpr int EPI = (NT / 64) * 32 * EPW * 4;
   constexpr int SMEM = NS * STAGE > EPI ? NS * STAGE : EPI;
-  static_assert(NS >= 1 && NS <= 4, "1 to 4 LDS stages (1: a single K step only)");
+  static_assert(NS >= 1 && NS <= 8, "LDS stages");
   static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0 && JB >= 1, "tile rows must fill whole load passes");
   static_assert(NT % 128 == 0, "swizzle assumes NT a multiple of 128");
   static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be 32x32 blocks");
@@ -329,26 +332,35 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
   const int mtile = t / p.nt;
   const int m0 = mtile * BM, n0 = (t - mtile * p.nt) * BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int lchunk = (tid & 7) ^ ((tid >> 4) & 7);   // logical K chunk this thread loads
   const int rbase = tid >> 3;                        // + j * NT / 8
   const int HoWo = p.Ho * p.Wo;
 
+  // per row group of this thread: the window origin (pixel and row / column;
+  // rows past M get an origin far outside the image, so every tap reads zero),
+  // and the pixel of src2
   int a_pix[JA], a_pix2[JA], a_ih[JA], a_iw[JA];
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
-    const int m = m0 + rbase + j * (NT / 8);
+    // (a 1x1 layer has no padding: there the last row stands in for rows
+    // past M, whose sums are not stored)
+    const int m = UNI && KS == 1 ? min(m0 + rbase + j * (NT / 8), M - 1) : m0 + rbase + j * (NT / 8);
     if (m < M) {
       const int img = m / HoWo;
       const int rem = m - img * HoWo;
       const int oh = rem / p.Wo, ow = rem - (rem / p.Wo) * p.Wo;
       const int simg = p.srows ? p.srows[img] : img;
-      const int s2img = p.s2rows ? p.s2rows[img] : img;
       a_ih[j] = oh * p.stride - p.pad;
       a_iw[j] = ow * p.stride - p.pad;
       a_pix[j] = (simg * p.H + a_ih[j]) * p.W + a_iw[j];
-      a_pix2[j] = (s2img * p.H2 + a_ih[j] * p.s2) * p.W2 + a_iw[j] * p.s2;
+      a_pix2[j] = 0;
+      if (KS == 1 && p.src2) {
+        const int s2img = p.s2rows ? p.s2rows[img] : img;
+        a_pix2[j] = (s2img * p.H2 + a_ih[j] * p.s2) * p.W2 + a_iw[j] * p.s2;
+      }
     } else {
       a_ih[j] = -0x4000;
       a_iw[j] = -0x4000;
@@ -356,49 +368,81 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
       a_pix2[j] = 0;
     }
   }
-  const uint16_t* wrow = p.w + (size_t)(n0 + rbase) * p.Kp + lchunk * 8;
 
   // this workgroup's K steps: [kb, kb + nk) of the layer's Kp / 64
   const int nk_all = p.Kp / 64;
   const int kb = split * nk_all / p.ksplit;
   const int nk = (split + 1) * nk_all / p.ksplit - kb;
 
-  auto issue = [&](int kt, int stage) __attribute__((always_inline)) {
-    char* sb = smem + stage * STAGE;
-    kt += kb;
-    // a folded projection's steps (the last kfold of the layout) come first
-    if (p.kfold) kt = kt < p.kfold ? kt + (nk_all - p.kfold) : kt - p.kfold;
-    const int kidx = kt * 64 + lchunk * 8;
-    int tap = 0, ci = kidx;
-    if constexpr (KS != 1) {
-      tap = kidx >> p.cin_log2;
-      ci = kidx & (p.cin - 1);
-    }
-    const int kh = tap / KS, kw = tap - (tap / KS) * KS;
-    const bool kok = kidx < p.K;
-    const uint16_t* sp = p.src;
-    int cs = p.cin1, co = ci;
-    if (ci >= p.cin1) {
-      sp = p.src2;
-      cs = p.cin2;
-      co = ci - p.cin1;
-    }
-    const int doff = kh * p.W + kw;
+  // A K step's loads: the JA row groups of the input, then the JB of the
+  // weights.  UNI: 64 divides the channels of each input tensor, so a step is
+  // one tap of one tensor for every lane: scalar bases, 32-bit offsets per
+  // lane, and the padding of a 3x3 layer from the buffer's range check (tensors
+  // below 2^31 bytes).  Else every lane finds its own tap and tensor, and padding comes
+  // from a page of zeros.
+  constexpr uint32_t kOut = 0xC0000000u;
+  struct Step {
+    int kt, tap, kh, kw;
+    bool second;
+  };
+  u32x4 abuf{};
+  uint32_t aofs[JA], aofs2[JA];
+  if constexpr (UNI) {
+    if (KS != 1) abuf = raw_buffer(p.src, p.src_bytes);
 #pragma unroll
     for (int j = 0; j < JA; ++j) {
-      const int ih = a_ih[j] + kh, iw = a_iw[j] + kw;
-      const bool ok = kok && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
-      const uint16_t* g = ok ? sp + (size_t)((ci >= p.cin1 ? a_pix2[j] : a_pix[j]) + doff) * cs + co : p.zeros;
-      __builtin_amdgcn_global_load_lds((const void*)g, (lds_void_ptr)(sb + (j * NT + wave * 64) * 16), 16, 0, 0);
+      aofs[j] = static_cast<uint32_t>(a_pix[j]) * (p.cin1 * 2) + lchunk * 16;
+      aofs2[j] = static_cast<uint32_t>(a_pix2[j]) * (p.cin2 * 2) + lchunk * 16;
     }
-#pragma unroll
-    for (int j = 0; j < JB; ++j) {
-      const uint16_t* g = wrow + (size_t)j * (NT / 8) * p.Kp + kt * 64;
-      __builtin_amdgcn_global_load_lds((const void*)g, (lds_void_ptr)(sb + A_BYTES + (j * NT + wave * 64) * 16), 16,
-                                       0, 0);
+  }
+  const uint16_t* const wbase = p.w + (size_t)n0 * p.Kp;
+  const uint32_t wofs = static_cast<uint32_t>(rbase * p.Kp + lchunk * 8) * 2;
+  auto step_of = [&](int kt) __attribute__((always_inline)) {
+    Step r;
+    kt += kb;
+    // a folded projection's steps (the last kfold of the layout) come first
+    if (KS == 1 && p.kfold) kt = kt < p.kfold ? kt + (nk_all - p.kfold) : kt - p.kfold;
+    r.kt = kt;
+    r.tap = KS == 1 ? 0 : (kt * 64) >> p.cin_log2;
+    r.kh = r.tap / KS;
+    r.kw = r.tap - r.kh * KS;
+    r.second = KS == 1 && kt * 64 >= p.cin1;
+    return r;
+  };
+  auto issue = [&](const Step& r, char* sb, int j) __attribute__((always_inline)) {
+    if (j >= JA) {
+      const int jb = j - JA;
+      load_lds16(wbase + ((size_t)jb * (NT / 8) * p.Kp + r.kt * 64), wofs, sb + A_BYTES + (jb * NT + wave * 64) * 16);
+    } else if constexpr (UNI) {
+      char* const d = sb + (j * NT + wave * 64) * 16;
+      if constexpr (KS == 1) {
+        load_lds16(r.second ? p.src2 + (r.kt * 64 - p.cin1) : p.src + r.kt * 64, r.second ? aofs2[j] : aofs[j], d);
+      } else {
+        const int ih = a_ih[j] + r.kh, iw = a_iw[j] + r.kw;
+        const bool ok = (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
+        const uint32_t tofs = static_cast<uint32_t>((r.kh * p.W + r.kw) * p.cin + (r.kt * 64 - (r.tap << p.cin_log2))) * 2;
+        buffer_lds16(abuf, ok ? aofs[j] + tofs : kOut, 0, d);
+      }
+    } else {
+      const int kidx = r.kt * 64 + lchunk * 8;
+      int tap = 0, ci = kidx;
+      if constexpr (KS != 1) {
+        tap = kidx >> p.cin_log2;
+        ci = kidx & (p.cin - 1);
+      }
+      const int kh = tap / KS, kw = tap - (tap / KS) * KS;
+      const int ih = a_ih[j] + kh, iw = a_iw[j] + kw;
+      const bool ok = kidx < p.K && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
+      const bool second = ci >= p.cin1;
+      const uint16_t* const g = (second ? p.src2 : p.src) +
+                                (size_t)((second ? a_pix2[j] : a_pix[j]) + kh * p.W + kw) * (second ? p.cin2 : p.cin1) +
+                                (second ? ci - p.cin1 : ci);
+      load_lds16(ok ? g : p.zeros, sb + (j * NT + wave * 64) * 16);
     }
   };
 
+  // A = weights (32 output channels), B = pixels: a lane's sums are 4
+  // consecutive channels of one pixel per group (channels 8q + 4 hi .. + 3)
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
@@ -407,151 +451,173 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-  const int lsw = (lane >> 1) & 7;
-  // operands of K sub-step s+1 are read from LDS while sub-step s's MFMAs run
-  auto compute = [&](int stage) __attribute__((always_inline)) {
-    const char* sa = smem + stage * STAGE + (wm * WTM + (lane & 31)) * 128;
-    const char* sbp = smem + stage * STAGE + A_BYTES + (wn * WTN + (lane & 31)) * 128;
-    bf16x8 af[2][TM], bfr[2][TN];
-    auto fetch = [&](int s, int slot) __attribute__((always_inline)) {
-      const int phys = ((2 * s + (lane >> 5)) ^ lsw) * 16;
+  const int lsw = (lane >> 1) & 7, hi = lane >> 5;
+  const int aadr = (wm * WTM + (lane & 31)) * 128 + ((hi ^ lsw) << 4);
+  const int badr = A_BYTES + (wn * WTN + (lane & 31)) * 128 + ((hi ^ lsw) << 4);
+  bf16x8 af[2][TM], bfr[2][TN];
+  auto fetch = [&](const char* st, int s, int f) __attribute__((always_inline)) {
+    if (f < TM)
+      af[s & 1][f] = *reinterpret_cast<const bf16x8*>(st + ((aadr ^ (s << 5)) + f * 4096));
+    else
+      bfr[s & 1][f - TM] = *reinterpret_cast<const bf16x8*>(st + ((badr ^ (s << 5)) + (f - TM) * 4096));
+  };
+  constexpr int NM = TM * TN, NL = JA + JB;
+  // the MFMAs of a step from stage `st`; LDS reads run one sub-step ahead, and
+  // with `more` the loads of step r into `ld` go out between the MFMAs
+  auto compute = [&](const char* st, auto more, const Step& r, char* ld) __attribute__((always_inline)) {
 #pragma unroll
-      for (int a = 0; a < TM; ++a) af[slot][a] = *reinterpret_cast<const bf16x8*>(sa + a * 32 * 128 + phys);
+    for (int f = 0; f < TM + TN; ++f) fetch(st, 0, f);
 #pragma unroll
-      for (int b = 0; b < TN; ++b) bfr[slot][b] = *reinterpret_cast<const bf16x8*>(sbp + b * 32 * 128 + phys);
-    };
-    fetch(0, 0);
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s + 1 < 4) fetch(s + 1, (s + 1) & 1);
+      for (int i = 0; i < NM; ++i) {
+        constexpr int PER = NM > 1 ? (2 * (TM + TN) + NM - 1) / NM : TM + TN;
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+        for (int f = i * PER; f < (i + 1) * PER && f < TM + TN; ++f)
+          if (s < 3) fetch(st, s + 1, f);
+        __builtin_amdgcn_sched_barrier(0);
+        acc[i / TN][i % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[s & 1][i % TN], af[s & 1][i / TN],
+                                                                      acc[i / TN][i % TN], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(more)::value) {
+          // NL loads over the first three sub-steps' MFMAs
+          constexpr int SLOTS = 3 * NM, PL = (NL + SLOTS - 1) / SLOTS;
+          const int q = s * NM + i;
 #pragma unroll
-        for (int b = 0; b < TN; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s & 1][a], bfr[s & 1][b], acc[a][b], 0, 0, 0);
-    }
+          for (int j = q * PL; j < (q + 1) * PL && j < NL; ++j) issue(r, ld, j);
+        }
+      }
+  };
+  auto issue_all = [&](int kt, char* sb) __attribute__((always_inline)) {
+    const Step r = step_of(kt);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) issue(r, sb, j);
   };
 
   // a folded projection: once its K steps are summed, each sum becomes the
   // projection's output as the unfused layer stores it (scale, shift, bf16
   // rounding), divided by the block's scale, so the block's own steps add
   // to it and the epilogue's scale / shift finish the residual sum
-  float fsp[TN], fbp[TN], finv[TN];
-  {
-    if (p.kfold) {
-#pragma unroll
-      for (int b = 0; b < TN; ++b) {
-        const int col = n0 + wn * WTN + b * 32 + (lane & 31);
-        const bool in = col < p.cout;
-        fsp[b] = in ? p.fsp[col] : 0.f;
-        fbp[b] = in ? p.fbp[col] : 0.f;
-        finv[b] = in ? p.finv[col] : 0.f;
-      }
-    }
-  }
   auto fold_round = [&]() __attribute__((always_inline)) {
-    {
 #pragma unroll
-      for (int a = 0; a < TM; ++a)
+    for (int b = 0; b < TN; ++b)
 #pragma unroll
-        for (int b = 0; b < TN; ++b)
+      for (int q = 0; q < 4; ++q) {
+        // one group's vectors at a time: all of them would not fit the
+        // registers (channels past the last one read zeros)
+        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t at = static_cast<uint32_t>(n0 + wn * WTN + 4 * hi) * 4 + (b * 32 + 8 * q) * 4, nb = p.cout * 4;
+        const u32x4 sp = buffer_load16(p.fsp, nb, at), bp = buffer_load16(p.fbp, nb, at), iv = buffer_load16(p.finv, nb, at);
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            acc[a][b][r] = bf2f(f2bf(fmaf(acc[a][b][r], fsp[b], fbp[b]))) * finv[b];
-    }
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int a = 0; a < TM; ++a)
+            acc[a][b][4 * q + e] = bf2f(f2bf(fmaf(acc[a][b][4 * q + e], __uint_as_float(sp[e]), __uint_as_float(bp[e])))) *
+                                   __uint_as_float(iv[e]);
+      }
   };
 
-  const bool partial = p.ksplit > 1;   // raw sums; the split reduction finishes them
+  const bool partial = !LEAN && p.ksplit > 1;   // raw sums; the split reduction finishes them
   // residual vectors of the rows and 8-channel groups this lane finishes in
   // the epilogue (below)
   constexpr int G = WTN / 8;           // 8-channel groups per row
-  constexpr int VI = 32 * G / 64;      // groups per lane in a 32-row block
-  uint4 rv[TM][VI];
-  auto load_res = [&]() __attribute__((always_inline)) {
+  constexpr int RPV = 64 / G;          // rows per pass
+  constexpr int VI = 32 / RPV;         // passes over a 32-row block
+  const int g8 = lane % G, col = n0 + wn * WTN + g8 * 8;
+  const bool cok = col < p.cout;
+  const int row0 = m0 + wm * WTM + lane / G;   // this lane's row in pass 0 of block 0
+  // scale and shift of the eight channels that this lane finishes (past the
+  // last channel: zeros), requested ahead of the main loop where there are
+  // registers for them
+  float sc[8], sh[8];
 #pragma unroll
-    for (int a = 0; a < TM; ++a)
+  for (int e = 0; e < 8; ++e) {
+    sc[e] = 1.0f;
+    sh[e] = 0.0f;
+  }
+  auto load8 = [&](float (&d)[8], const float* g) __attribute__((always_inline)) {
+    const u32x4 lo = buffer_load16(g, p.cout * 4, col * 4), hv = buffer_load16(g, p.cout * 4, col * 4 + 16);
 #pragma unroll
-      for (int v = 0; v < VI; ++v) {
-        const int idx = v * 64 + lane;
-        const int rl = idx / G, g = idx - (idx / G) * G;
-        const int row = m0 + wm * WTM + a * 32 + rl;
-        const int col = n0 + wn * WTN + g * 8;
-        rv[a][v] = (row < M && col < p.cout)
-                       ? *reinterpret_cast<const uint4*>(p.res + row_at(p.rrows, row, HoWo) * p.cout + col)
-                       : make_uint4(0, 0, 0, 0);
+    for (int e = 0; e < 4; ++e) {
+      d[e] = __uint_as_float(lo[e]);
+      d[4 + e] = __uint_as_float(hv[e]);
+    }
+  };
+  auto load_ss = [&]() __attribute__((always_inline)) {
+    if (!partial && p.scale) load8(sc, p.scale);
+    if (!partial && p.shift) load8(sh, p.shift);
+  };
+  if (NS > 1) load_ss();
+  uint4 rv[2][VI];
+  // LEAN: rows of the tile through buffers that end with the layer's last
+  // row, at 32-bit offsets; a channel past the last one gets an offset that
+  // no buffer reaches
+  const uint32_t tbytes = static_cast<uint32_t>(min(BM, M - m0)) * p.cout * 2;
+  const uint32_t tofs = cok ? static_cast<uint32_t>((row0 - m0) * p.cout + col) * 2 : kOut;
+  const uint32_t pofs = static_cast<uint32_t>(RPV * p.cout) * 2;   // from one pass to the next
+  auto load_res = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < VI; ++v) {
+      if constexpr (LEAN) {
+        const u32x4 w = buffer_load16(p.res + static_cast<size_t>(m0) * p.cout, tbytes, tofs + (a * VI + v) * pofs);
+        rv[a & 1][v] = make_uint4(w[0], w[1], w[2], w[3]);
+      } else {
+        const int row = row0 + a * 32 + v * RPV;
+        rv[a & 1][v] = (row < M && cok) ? *reinterpret_cast<const uint4*>(p.res + row_at(p.rrows, row, HoWo) * p.cout + col)
+                                        : make_uint4(0, 0, 0, 0);
       }
+    }
   };
 
-  // NS-stage pipeline: the loads of step kt+NS-1 are issued while step kt
-  // is computed; the stage they fill was read in step kt-1, which every wave
-  // finished before the barrier of step kt
-#pragma unroll
-  for (int i = 0; i < NS - 1; ++i)
-    if (i < nk) issue(i, i);
   if constexpr (NS == 1) {
     // one stage, the K steps one after another (one step, or a few on a
     // memory-bound layer): a small LDS footprint, more workgroups per CU,
     // whose number (not the bytes in flight per workgroup) sets the speed
     // of these layers
     for (int kt = 0; kt < nk; ++kt) {
-      if (kt) __syncthreads();   // every wave is done reading the stage
-      issue(kt, 0);
+      if (kt) lds_barrier();     // every wave is done reading the stage
+      issue_all(kt, smem);
       wait_vm_barrier<0>();
-      compute(0);
+      compute(smem, std::false_type{}, Step{}, nullptr);
       if (kt + 1 == p.kfold) fold_round();
-    }
-  } else if (NS == 2) {
-    // rounds of two K steps requested together: the second step's latency
-    // overlaps the first's, and a layer of nk steps waits on ceil(nk / 2)
-    // round trips (measured 5-25 % faster than keeping one step in flight
-    // behind the MFMAs, on every layer shape tried, and ahead of four
-    // pipelined stages on 64 x 64 tiles)
-    for (int kt = 0; kt < nk; kt += 2) {
-      if (kt) {
-        __syncthreads();   // every wave is done reading both stages
-        issue(kt, 0);
-      }
-      if (kt + 1 < nk) {
-        issue(kt + 1, 1);
-        wait_vm_barrier<JA + JB>();   // step kt has landed; kt + 1 may be in flight
-      } else {
-        wait_vm_barrier<0>();
-      }
-      compute(0);
-      if (kt + 1 == p.kfold) fold_round();
-      if (kt + 1 < nk) {
-        wait_vm_barrier<0>();
-        compute(1);
-        if (kt + 2 == p.kfold) fold_round();
-      }
     }
   } else {
-    for (int kt = 0; kt < nk; ++kt) {
-      if (kt + NS - 2 < nk)
-        wait_vm_barrier<(NS - 2) * (JA + JB)>();   // steps kt+1 .. kt+NS-2 may stay in flight
-      else
-        wait_vm_barrier<0>();
-      if (kt + NS - 1 < nk) issue(kt + NS - 1, (kt + NS - 1) % NS);
-      compute(kt % NS);
+    // step kt's stage has landed once at most the NS - 2 steps after it are
+    // in flight; the stage that step kt + NS - 1 fills was read in step
+    // kt - 1, which every wave finished before the barrier of step kt
+#pragma unroll
+    for (int i = 0; i < NS - 1; ++i)
+      if (i < nk) issue_all(i, smem + i * STAGE);
+    int cur = 0, ld = (NS - 1) * STAGE;
+    int kt = 0;
+    for (; kt + NS - 1 < nk; ++kt) {
+      const Step r = step_of(kt + NS - 1);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * NL) : "memory");
+      compute(smem + cur, std::true_type{}, r, smem + ld);
+      cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+      ld = ld + STAGE == NS * STAGE ? 0 : ld + STAGE;
+      if (kt + 1 == p.kfold) fold_round();
+    }
+    for (; kt < nk; ++kt) {
+      all_barrier();
+      compute(smem + cur, std::false_type{}, Step{}, nullptr);
+      cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
       if (kt + 1 == p.kfold) fold_round();
     }
   }
 
-  // epilogue through LDS: each wave stages 32 x WTN fp32 values (scale and
-  // shift applied) in its own region, then every lane finishes 8
-  // consecutive channels of a row (residual, activation, rounding) and
-  // writes them with one 16-byte store.  The residual vectors of all the
-  // wave's rows are requested first, so their latency overlaps the staging.
-  __syncthreads();   // the main loop's last tiles are no longer read
+  // epilogue through LDS: each wave stages 32 x WTN raw sums in its own
+  // region, then every lane finishes 8 consecutive channels of a row (scale
+  // and shift, residual, activation, rounding) and writes them with one
+  // 16-byte store.  The residual vectors of a block of rows are requested
+  // before the stores of the block before it: loads and stores complete in
+  // one order.  A wave's LDS operations run in order, so its staging needs no
+  // waits of its own.
+  const bool res = p.res && !partial;
+  if (NS == 1) load_ss();
+  if (res) load_res(0);
+  seen_barrier();   // the main loop's last tiles are no longer read
   float* ep = reinterpret_cast<float*>(smem) + wave * 32 * EPW;
-  float sc[TN], sh[TN];
-#pragma unroll
-  for (int b = 0; b < TN; ++b) {
-    const int col = n0 + wn * WTN + b * 32 + (lane & 31);
-    sc[b] = (!partial && p.scale && col < p.cout) ? p.scale[col] : 1.0f;
-    sh[b] = (!partial && p.shift && col < p.cout) ? p.shift[col] : 0.0f;
-  }
-  if (p.res && !partial) load_res();
   // the activation is chosen once, outside the epilogue's loops
   auto epilogue = [&](auto act_c) __attribute__((always_inline)) {
     constexpr int ACT = decltype(act_c)::value;
@@ -560,25 +626,27 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
 #pragma unroll
       for (int b = 0; b < TN; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          ep[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EPW + b * 32 + (lane & 31)] = fmaf(acc[a][b][r], sc[b], sh[b]);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own staging region: in-order LDS
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(ep + (lane & 31) * EPW + b * 32 + 8 * q + 4 * hi) =
+              make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
+      if (a + 1 < TM && res) load_res(a + 1);
+      asm volatile("" ::: "memory");
 #pragma unroll
       for (int v = 0; v < VI; ++v) {
-        const int idx = v * 64 + lane;
-        const int rl = idx / G, g = idx - (idx / G) * G;
-        const int row = m0 + wm * WTM + a * 32 + rl;
-        const int col = n0 + wn * WTN + g * 8;
-        if (row < M && col < p.cout) {
-          const float4 lo = *reinterpret_cast<const float4*>(ep + rl * EPW + g * 8);
-          const float4 hi = *reinterpret_cast<const float4*>(ep + rl * EPW + g * 8 + 4);
-          float vv[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-          if (partial) {
+        const int rl = v * RPV + lane / G;
+        const int row = row0 + a * 32 + v * RPV;
+        if (LEAN || (row < M && cok)) {
+          const float4 lo = *reinterpret_cast<const float4*>(ep + rl * EPW + g8 * 8);
+          const float4 hv = *reinterpret_cast<const float4*>(ep + rl * EPW + g8 * 8 + 4);
+          if (!LEAN && partial) {
             float* d = p.part + (size_t)split * p.M * p.cout + (size_t)row * p.cout + col;
             *reinterpret_cast<float4*>(d) = lo;
-            *reinterpret_cast<float4*>(d + 4) = hi;
+            *reinterpret_cast<float4*>(d + 4) = hv;
             continue;
           }
+          float vv[8] = {lo.x, lo.y, lo.z, lo.w, hv.x, hv.y, hv.z, hv.w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) vv[e] = fmaf(vv[e], sc[e], sh[e]);
           if constexpr (ACT == ACT_LSTM) {
             // the 8 values are the gates of cells u and u + 1 (input,
             // forget, cell, output each); cell state float32, h bf16
@@ -593,9 +661,8 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
             *reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(p.dst) + oc) = pack_bf16(h0, h1);
             continue;
           }
-          const size_t o = row_at(p.drows, row, HoWo) * p.cout + col;
           if (p.res) {
-            const uint32_t rw[4] = {rv[a][v].x, rv[a][v].y, rv[a][v].z, rv[a][v].w};
+            const uint32_t rw[4] = {rv[a & 1][v].x, rv[a & 1][v].y, rv[a & 1][v].z, rv[a & 1][v].w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               vv[2 * q] += __uint_as_float(rw[q] << 16);
@@ -604,8 +671,8 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
           }
 #pragma unroll
           for (int q = 0; q < 8; ++q) vv[q] = act_t<ACT>(vv[q]);
-          if (p.out_f32) {
-            float* d = static_cast<float*>(p.dst) + o;
+          if (!LEAN && p.out_f32) {
+            float* d = static_cast<float*>(p.dst) + row_at(p.drows, row, HoWo) * p.cout + col;
             *reinterpret_cast<float4*>(d) = make_float4(vv[0], vv[1], vv[2], vv[3]);
             *reinterpret_cast<float4*>(d + 4) = make_float4(vv[4], vv[5], vv[6], vv[7]);
           } else {
@@ -614,12 +681,16 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
             ov.y = pack_bf16(vv[2], vv[3]);
             ov.z = pack_bf16(vv[4], vv[5]);
             ov.w = pack_bf16(vv[6], vv[7]);
-            *reinterpret_cast<uint4*>(static_cast<uint16_t*>(p.dst) + o) = ov;
+            if constexpr (LEAN)
+              buffer_store16(static_cast<uint16_t*>(p.dst) + static_cast<size_t>(m0) * p.cout, tbytes,
+                             tofs + (a * VI + v) * pofs, u32x4{ov.x, ov.y, ov.z, ov.w});
+            else
+              *reinterpret_cast<uint4*>(static_cast<uint16_t*>(p.dst) + row_at(p.drows, row, HoWo) * p.cout + col) = ov;
             if (p.gap) {
               // the stored values back into the staging rows, for the
               // chunk's column sums below
               const uint32_t ow[4] = {ov.x, ov.y, ov.z, ov.w};
-              float* e8 = ep + rl * EPW + g * 8;
+              float* e8 = ep + rl * EPW + g8 * 8;
               *reinterpret_cast<float4*>(e8) = make_float4(__uint_as_float(ow[0] << 16), __uint_as_float(ow[0] & 0xffff0000u),
                                                            __uint_as_float(ow[1] << 16), __uint_as_float(ow[1] & 0xffff0000u));
               *reinterpret_cast<float4*>(e8 + 4) = make_float4(__uint_as_float(ow[2] << 16), __uint_as_float(ow[2] & 0xffff0000u),
@@ -631,7 +702,7 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
       if constexpr (ACT != ACT_LSTM) {
         const int row0 = m0 + wm * WTM + a * 32;   // a 32-row chunk of layer rows
         if (p.gap && !partial && row0 < M) {
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own rows: in-order LDS
+          asm volatile("" ::: "memory");   // the wave's own rows: in-order LDS
           // rows before `bnd` belong to the chunk's first image, the rest to
           // the next one (an image has at least 32 rows; rows past M land in
           // the second sum of the last image's chunk, which is never read)
@@ -655,17 +726,17 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
           }
         }
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next block's staging
+      asm volatile("" ::: "memory");   // the reads stay before the next block's staging
     }
   };
   if (p.act == ACT_RELU)
     epilogue(std::integral_constant<int, ACT_RELU>{});
-  else if (p.act == ACT_GELU)
-    epilogue(std::integral_constant<int, ACT_GELU>{});
-  else if (p.act == ACT_TANH)
-    epilogue(std::integral_constant<int, ACT_TANH>{});
-  else if (p.act == ACT_LSTM)
-    epilogue(std::integral_constant<int, ACT_LSTM>{});
+  else if (!LEAN && p.act == ACT_GELU)
+    epilogue(std::integral_constant<int, LEAN ? ACT_NONE : ACT_GELU>{});
+  else if (!LEAN && p.act == ACT_TANH)
+    epilogue(std::integral_constant<int, LEAN ? ACT_NONE : ACT_TANH>{});
+  else if (!LEAN && p.act == ACT_LSTM)
+    epilogue(std::integral_constant<int, LEAN ? ACT_NONE : ACT_LSTM>{});
   else
     epilogue(std::integral_constant<int, ACT_NONE>{});
 }
@@ -1100,67 +1171,84 @@ void dispatch_staged(const TileCfg& c, const ConvP& p, hipStream_t s) {
   }
 }
 
-// direct-to-LDS kernel.  A workgroup's LDS (two stages) sets how many fit
-// on a CU: two of 128 x 128 (64 KB), three of 128 x 64 (48 KB); a grid runs
-// in ceil(tiles / resident) rounds.  Tiles are compared by rounds times tile
-// area, the time of the slowest CU (measured on the layer shapes of the
-// workloads; 256 x 256 tiles lost on every one of them)
-TileCfg choose_lds(int M, int cout, int Kp) {
-  const TileCfg c128{128, 128, 2, 2}, c12864{128, 64, 2, 2}, c64{64, 64, 2, 2}, c64128{64, 128, 2, 2},
-      c32{128, 32, 4, 1};
-  if (cout < 64) return c32;
-  // one K step: memory-bound; 128 x 64 tiles (24 KB of LDS, five
-  // workgroups per CU by registers) keep the most rows in flight (measured
-  // against 128 x 128, 64 x 128, 64 x 64 and 256 x 64 on the ResNet-50 1x1
-  // layers)
-  if (Kp <= 64) return c12864;
-  constexpr long kCUs = 256;
-  const long r128 = (tiles_of(c128, M, cout) + 2 * kCUs - 1) / (2 * kCUs);
-  const long t12864 = tiles_of(c12864, M, cout), r12864 = (t12864 + 3 * kCUs - 1) / (3 * kCUs);
-  // few tiles (a layer bound by its chains of K rounds): 64 x 64 below ~1.5
-  // tiles of 128 x 64 per CU, 64 x 128 below four (measured with rounds of
-  // two K steps: ResNet-50's strided stage-3 3x3 49 -> 42 us, its stage-3/4
-  // reductions and stage-4 expansions 4-10 % faster than 128 x 64)
-  if (t12864 < 400) return c64;
-  if (t12864 < 1024 && cout % 128 == 0) return c64128;
-  // 128 x 128 when its rounds of double-area tiles take no longer, or when
-  // one tile column spans a short-K layer's channels, so that each input
-  // pixel (the bulk of its traffic) is fetched by one workgroup
-  if (cout >= 128 && (2 * r128 <= r12864 || (cout == 128 && Kp <= 256))) return c128;
-  return c12864;
+// Tile and stages of the direct-to-LDS kernel.
+struct LdsCfg {
+  int bm, bn, ns;
+};
+
+// One LDS stage, the K steps in turn, where the number of workgroups that a CU
+// holds bounds the layer: a spatial layer with at least 1024 tiles of 128 x 64
+// (and K <= 1024 when it is a 1x1 layer).  Measured there (us, 128 x 64 | 128 x
+// 128 | 128 x 256, before: 128 x 64 or 128 x 256 with a wait for the stores of
+// a row before the next): 256 images of 56x56, 64 -> 256 with a residual 183 |
+// 166 | 167, before 175; 182 of 28x28, 128 -> 512 with one 77 | 66 | 74, 80;
+// 182 of 56x56, 256 -> 128 94 | 87, 100; 107 of 14x14, 256 -> 1024 34 | 28 |
+// 33, 37; 529 of 16x16, 128 -> 256, strided 3x3 30 | 27 | 33, 36; 300 of 14x14,
+// 1024 -> 256 56 | 51 | 46, 60.  The other layers are bound by their chains of
+// K steps and by the operand bytes per step.  Measured (us, tile and stages):
+//   20972 rows x 256, K 1024 (164 tiles of 128 x 256): 128 x 256, three stages
+//     18.4; 128 x 128 19.1; 64 x 128 20.9.  20972 x 256, K 2304, strided 3x3:
+//     32.3, 36.4, 37.3
+//   4096 x 1024, K 2048 (256 tiles of 128 x 128): 128 x 128, three stages (one
+//     workgroup per CU) 21.7, two 28.4; 64 x 128 24.6
+//   2499 x 512, K 2048 (160 tiles of 64 x 128): 64 x 128 14.2; 64 x 64 14.7;
+//     128 x 128 18.5.  4080 x 512, K 2304 (256): 16.7, 17.6, 23.6
+//   1024 x 1024, K 2048 (128 tiles of 64 x 128): 64 x 64, four stages 11.5;
+//     64 x 128 14.6.  3136 x 256, K 1024: 7.8, 9.2
+LdsCfg choose_lds(int M, int cout, int Kp, int k, bool one) {
+  auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((cout + bn - 1) / bn); };
+  if (cout < 64) return {128, 32, 3};
+  if (one) return cout % 256 == 0 && k == 1 && Kp >= 1024 ? LdsCfg{128, 256, 1} : cout % 128 == 0 ? LdsCfg{128, 128, 1} : LdsCfg{128, 64, 1};
+  if (cout % 256 == 0 && tiles(128, 256) >= 160) return {128, 256, 3};
+  if (cout % 128 == 0) {
+    const long t = tiles(128, 128);
+    if (t >= 192) return {128, 128, t <= 256 ? 3 : 2};
+    if (tiles(64, 128) >= 160) return {64, 128, 3};
+  } else if (tiles(128, 64) >= 256) {
+    return {128, 64, 3};
+  }
+  return {64, 64, 4};
 }
 
-// stages: one (`one`, 128 x 64 or 128 x 256 tiles only: the K steps taken
-// in turn) where the workgroups a CU holds bound the layer, five with one
-// 24 KB stage against three with two: measured 2-20 % faster on the
-// ResNet-50 1x1 shapes with many tiles and 8-16 % on its strided 3x3
-// layers with 2.5 or more tiles per CU (slower with fewer); else two,
-// filled in rounds of two K steps
-template <int BM, int BN, int WM, int WN, int KS>
-void go_lds(const ConvP& p, hipStream_t s, int S, bool one) {
-  const dim3 grid(p.mt * p.nt * S);
-  if (one && S == 1) {
-    if constexpr (BM == 128 && (BN == 64 || BN == 256))
-      hipLaunchKernelGGL((conv_lds_kernel<BM, BN, WM, WN, KS, 1>), grid, dim3(64 * WM * WN), 0, s, p);
-    else
-      throw std::invalid_argument("conv_bf16: the one-stage implicit GEMM takes 128 x 64 or 128 x 256 tiles only");
-  } else if constexpr (BN == 256) {
-    throw std::invalid_argument("conv_bf16: 128 x 256 tiles are one-stage only");
-  } else {
-    hipLaunchKernelGGL((conv_lds_kernel<BM, BN, WM, WN, KS, 2>), grid, dim3(64 * WM * WN), 0, s, p);
+// LEAN: ReLU or no activation, bf16 output in the layer's own rows, no K split
+// (fewer registers, and stores and residual through range-checked buffers).
+// UNI: scalar taps and sources (below).
+template <int BM, int BN, int WM, int WN, int KS, int NS, bool LEAN, bool UNI = true>
+void go_lds(const ConvP& p, hipStream_t s, int S) {
+  hipLaunchKernelGGL((conv_lds_kernel<BM, BN, WM, WN, KS, NS, LEAN, UNI>), dim3(p.mt * p.nt * S), dim3(64 * WM * WN), 0,
+                     s, p);
+}
+
+template <int KS, bool LEAN>
+void dispatch_uni(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
+  switch ((c.bm * 1000 + c.bn) * 10 + c.ns) {
+    case 1281281: go_lds<128, 128, 2, 2, KS, 1, LEAN>(p, s, S); break;
+    case 1281282: go_lds<128, 128, 2, 2, KS, 2, LEAN>(p, s, S); break;
+    case 1281283: go_lds<128, 128, 2, 2, KS, 3, LEAN>(p, s, S); break;
+    case 1280641: go_lds<128, 64, 2, 2, KS, 1, LEAN>(p, s, S); break;
+    case 1280643: go_lds<128, 64, 2, 2, KS, 3, LEAN>(p, s, S); break;
+    case 1282561: go_lds<128, 256, 2, 4, KS, 1, LEAN>(p, s, S); break;
+    case 1282563: go_lds<128, 256, 2, 4, KS, 3, LEAN>(p, s, S); break;
+    case 641283: go_lds<64, 128, 2, 2, KS, 3, LEAN>(p, s, S); break;
+    case 640644: go_lds<64, 64, 2, 2, KS, 4, LEAN>(p, s, S); break;
+    default: go_lds<128, 32, 4, 1, KS, 3, LEAN>(p, s, S); break;
   }
 }
 
+// lanes with taps and sources of their own: 64 x 64, 128 x 64 or 128 x 32 tiles
 template <int KS>
-void dispatch_lds(const TileCfg& c, const ConvP& p, hipStream_t s, int S = 1, bool one = false) {
-  switch (c.bm * 1000 + c.bn) {
-    case 128128: go_lds<128, 128, 2, 2, KS>(p, s, S, one); break;
-    case 128064: go_lds<128, 64, 2, 2, KS>(p, s, S, one); break;
-    case 128256: go_lds<128, 256, 2, 4, KS>(p, s, S, one); break;
-    case 64064: go_lds<64, 64, 2, 2, KS>(p, s, S, one); break;
-    case 64128: go_lds<64, 128, 2, 2, KS>(p, s, S, one); break;
-    default: go_lds<128, 32, 4, 1, KS>(p, s, S, one); break;
-  }
+void dispatch_lanes(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
+  if (c.bn == 32) go_lds<128, 32, 4, 1, KS, 3, false, false>(p, s, S);
+  else if (c.bm == 64) go_lds<64, 64, 2, 2, KS, 4, false, false>(p, s, S);
+  else go_lds<128, 64, 2, 2, KS, 3, false, false>(p, s, S);
+}
+
+void dispatch_lds(int k, const LdsCfg& c, const ConvP& p, hipStream_t s, int S, bool uni) {
+  const bool lean = S == 1 && !p.out_f32 && !p.rrows && !p.drows && (p.act == ACT_RELU || p.act == ACT_NONE);
+  if (k == 7) dispatch_lanes<7>(c, p, s, S);
+  else if (!uni) k == 1 ? dispatch_lanes<1>(c, p, s, S) : dispatch_lanes<3>(c, p, s, S);
+  else if (lean) k == 1 ? dispatch_uni<1, true>(c, p, s, S) : dispatch_uni<3, true>(c, p, s, S);
+  else k == 1 ? dispatch_uni<1, false>(c, p, s, S) : dispatch_uni<3, false>(c, p, s, S);
 }
 
 // Tile geometry of the halo kernels: BM-pixel tiles of R whole rows of one
@@ -1396,34 +1484,32 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
     const int S = conv_ksplit(a.Ho, a.Wo, a.cout, p.K, a.out_f32 != 0);
     const bool split = S > 1 && a.splitws && !a.res_rows && !a.dst_rows && !a.kfold && !special &&
                        a.splitws_bytes >= static_cast<size_t>(S) * p.M * a.cout * sizeof(float);
-    // one LDS stage on 128 x 64 tiles: a spatial layer with at least 1024
-    // such tiles (and K <= 1024 for a 1x1 layer); fewer tiles wait on fewer
-    // round trips in rounds of two K steps (the ResNet-50 stage-3/4 layers
-    // 4-15 % faster); on 128 x 256
-    // tiles (eight waves, whole 512-byte row pieces per workgroup: the
-    // output-heavy layers' stores were the limit) when Cout is a multiple of
-    // 256 and there are at least 512 of them (measured 4-15 % faster on the
-    // ResNet-50 expansions and folded projections with 2.5 or more such
-    // tiles per CU, slower with fewer)
+    // one LDS stage: a spatial layer with at least 1024 tiles of 128 x 64 (and
+    // K <= 1024 for a 1x1 layer)
     const long t12864 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 63) / 64);
-    const long t128256 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 255) / 256);
     const bool one = !split && a.cout >= 64 && a.Ho * a.Wo > 1 && t12864 >= 1024 && (a.k != 1 || p.Kp <= 1024);
-    const bool wide = one && a.cout % 256 == 0 && t128256 >= 512;
-    const TileCfg c = split ? (a.cout % 128 == 0 ? TileCfg{128, 128, 2, 2} : TileCfg{128, 64, 2, 2})
-                      : wide ? TileCfg{128, 256, 2, 4}
-                      : one ? TileCfg{128, 64, 2, 2}
-                            : choose_lds(Mh, a.cout, p.Kp);
+    // scalar taps and offsets (UNI): 64 divides the channels of each input
+    // tensor, and the tensors lie below 2^31 bytes
+    const long b1 = static_cast<long>(a.src_rows ? a.list_rows : a.n) * a.H * a.W * a.cin1 * 2;
+    const long b2 = a.src2 ? static_cast<long>(a.src2_rows ? a.src2_list_rows : a.n) * p.H2 * p.W2 * a.cin2 * 2 : 0;
+    const bool uni = a.k != 7 && a.cin1 % 64 == 0 && (!a.src2 || a.cin2 % 64 == 0) && b1 < 0x7fffffffL &&
+                     b2 < 0x7fffffffL && (!a.src_rows || a.list_rows > 0) && (!a.src2_rows || a.src2_list_rows > 0);
+    p.src_bytes = static_cast<uint32_t>(b1);
+    // a split layer: 64 x 64 or 64 x 128 tiles while the four ranges of 128 x
+    // 128 tiles leave CUs idle (60 images of 4x4x512: 17 us against 24; 255
+    // images, 512 workgroups of 128 x 128: 39 against 42)
+    const long t128 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 127) / 128);
+    LdsCfg c = !split                                 ? choose_lds(Mh, a.cout, p.Kp, a.k, one)
+               : a.cout % 128 == 0 && S * t128 >= 256 ? LdsCfg{128, 128, 2}
+               : a.cout % 128 == 0                    ? LdsCfg{64, 128, 3}
+                                                      : LdsCfg{128, 64, 3};
+    if (!uni && c.bn > 64) c = {c.bm, 64, 3};
     p.mt = (p.M + c.bm - 1) / c.bm;
     p.nt = (a.cout + c.bn - 1) / c.bn;
     if (split) {
       p.ksplit = S;
       p.part = a.splitws;
-      if (a.k == 1)
-        dispatch_lds<1>(c, p, s, S);
-      else if (a.k == 3)
-        dispatch_lds<3>(c, p, s, S);
-      else
-        dispatch_lds<7>(c, p, s, S);
+      dispatch_lds(a.k, c, p, s, S, uni);
       const size_t items = static_cast<size_t>(p.M) * (a.cout / 8);
       const dim3 fgrid(static_cast<unsigned>((items + 255) / 256));
       auto finish = [&](auto k) {
@@ -1439,12 +1525,7 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
       return false;
     }
     if (a.gap_part && !a.out_f32 && !a.dst_rows && a.act != ACT_LSTM && a.Ho * a.Wo >= 32) p.gap = a.gap_part;
-    if (a.k == 1)
-      dispatch_lds<1>(c, p, s, 1, one);
-    else if (a.k == 3)
-      dispatch_lds<3>(c, p, s, 1, one);
-    else
-      dispatch_lds<7>(c, p, s, 1, one);
+    dispatch_lds(a.k, c, p, s, 1, uni);
     return p.gap != nullptr;
   }
   const TileCfg c = a.cout >= 128 ? choose(kWide, Mh, a.cout)

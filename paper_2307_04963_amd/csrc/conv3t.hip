@@ -158,12 +158,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     sc[e] = 1.0f;
     sh[e] = 0.0f;
   }
-  if (p.scale)
+  auto load8 = [&](float (&d)[8], const float* g) __attribute__((always_inline)) {
+    const u32x4 lo = buffer_load16(g, p.cout * 4, col * 4), hv = buffer_load16(g, p.cout * 4, col * 4 + 16);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sc[e] = p.scale[col + e];
-  if (p.shift)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sh[e] = p.shift[col + e];
+    for (int e = 0; e < 4; ++e) {
+      d[e] = __uint_as_float(lo[e]);
+      d[4 + e] = __uint_as_float(hv[e]);
+    }
+  };
+  if (p.scale) load8(sc, p.scale);
+  if (p.shift) load8(sh, p.shift);
 
   f32x16 acc[TB][TA];
 #pragma unroll

@@ -62,6 +62,7 @@ struct ConvArgs {
   const int32_t* res_rows = nullptr;
   const int32_t* dst_rows = nullptr;
   int list_rows = 0;     // rows of the tensors read or written through a list (0: no list)
+  int src2_list_rows = 0;   // the same for src2
   float* splitws = nullptr;         // K-split partial sums (conv_ksplit_bytes), or null: no split
   size_t splitws_bytes = 0;
   const float* cell_in = nullptr;   // ACT_LSTM: old cell state, or null (zeros)
