@@ -154,6 +154,8 @@ void gap_chunks(const float* Q, int n, int HW, int C, float* G, hipStream_t s, c
 // max-pool without ReLU).
 bool conv_rgb_stem_fits(int H, int W, int cin, int cout, int k, int stride, int pad);
 bool conv_rgb_stem(const ConvArgs& a, hipStream_t s);
+// its launch with the max-pool fused in, for arguments that it takes (ReLU)
+void conv_stem_pool(const ConvArgs& a, hipStream_t s);
 
 // 3x3 / stride-1 / pad-1 layers with 16 -> 16 or 32 -> 32 channels on 16- or
 // 32-pixel-wide images (row lists and device counts allowed): a halo kernel
