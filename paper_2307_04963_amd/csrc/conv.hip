@@ -1476,6 +1476,12 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
   // (image mode) or the implicit GEMM
   const bool listed = a.src_rows || a.src2_rows || a.res_rows || a.dst_rows;
   if (conv3_narrow(a, s)) return false;   // 16 / 32 channels: row lists allowed
+  // 64 -> 64 channels on few pixels: the tile kernel, whose workgroups start
+  // without loading all weights first (us, register-weight kernel | tiles: 500
+  // images of 8x8 9.4 | 7.9, 20 of 56x56 12.5 | 9.7, 300 of 14x14 11.8 | 9.0, 64
+  // of 32x32 12.0 | 10.8; 735 tiles of 128 pixels and more: 15.0 | 15.2, 14.4 |
+  // 16.4)
+  if (vec_out && !listed && a.cin == 64 && a.cout == 64 && Mh <= 600 * 128 && conv3_tiles(a, s)) return false;
   if (vec_out && (listed ? conv3_wres(a, s) : (conv3_wres(a, s) || conv3_tiles(a, s)))) return false;
   if (vec_out) {
     // deep K on few pixels per image: K ranges of one tile on several

@@ -22,7 +22,12 @@ CASES = [
     (170, 14, 14, 128, 64, 3, 1, 1, False, 1),   # 64 output channels
     (1, 5, 5, 64, 128, 3, 1, 1, True, 1),        # 64 x 64 tiles: one tile, 25 of 64 pixels
     (3, 3, 43, 64, 128, 3, 1, 1, False, 1),
-    (5, 2, 65, 64, 64, 3, 1, 1, False, 1),       # (64 -> 64 keeps the register-weight kernel)
+    (5, 2, 65, 64, 64, 3, 1, 1, False, 1),       # 64 -> 64 channels on few pixels: 64 x 64 tiles
+    (6, 56, 56, 64, 64, 3, 1, 1, True, 1),
+    (257, 11, 11, 64, 64, 3, 1, 1, True, 2),     # 128 x 64 tiles
+    (600, 8, 16, 64, 64, 3, 1, 1, True, 1),      # the last tile count they take
+    (601, 8, 16, 64, 64, 3, 1, 1, True, 1),      # one more: the register-weight kernel
+    (2, 5, 90, 64, 64, 3, 1, 1, False, 1),       # too wide for a patch: the register-weight kernel
     (5, 2, 65, 128, 64, 3, 1, 1, False, 1),      # two rows per image
     (4, 70, 2, 64, 128, 3, 1, 1, True, 1),       # two pixels per row
     (13, 7, 7, 256, 128, 3, 1, 1, True, 0),      # four input chunks
