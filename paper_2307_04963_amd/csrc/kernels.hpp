@@ -220,10 +220,12 @@ void exit_head_sliced(const float* G, int n, int K, const float* Wt, const float
 // Fused exit head for small heads (C <= 2048 and a multiple of 4, ncls <=
 // 1024): pooling, head linear on the weights as stored W [ncls][C] (16-byte
 // aligned rows), and the exit decision, up to 8 rows per workgroup.  Same
-// outputs as gap_bf16 + linear_t_f32 + exit_decide.
+// outputs as gap_bf16 + linear_t_f32 + exit_decide.  counts, when set, receives
+// the branch counts of a final exit (every live row, 0).
 void exit_head(const void* x, bool bf16, int n, int HW, int C, const float* W, const float* bias, int ncls,
                const float* T, float tau, int final_, int head, const int32_t* orig, uint8_t* flags, float* logits,
-               int n_out, dycl_record* rec, hipStream_t s, const int32_t* nc = nullptr, int nhint = 0);
+               int n_out, dycl_record* rec, hipStream_t s, const int32_t* nc = nullptr, int nhint = 0,
+               int32_t* counts = nullptr);
 
 // Gate: q = sigmoid(u . GAP(x) + v); flag = q > thr (execute); skipped rows set
 // bit `gate` of their record.
@@ -276,6 +278,12 @@ struct MoveSet {
 };
 void move_rows_multi(const MoveSet& set, const int32_t* dst_idx, const int32_t* src_idx, int n, hipStream_t s,
                      const int32_t* nc = nullptr);
+
+// compact, then move_rows_multi(set, null, idx0) of the rows with a clear
+// flag, in one launch, for few rows of little data (compact_move_fits)
+bool compact_move_fits(int n, const MoveSet& set);
+void compact_move(const uint8_t* flags, const int32_t* orig, int n, int32_t* idx1, int32_t* org1, int32_t* idx0,
+                  int32_t* org0, int32_t* counts, const MoveSet& set, hipStream_t s, const int32_t* nc = nullptr);
 
 void maxpool3s2_bf16(const uint16_t* x, int n, int H, int W, int C, uint16_t* y, hipStream_t s,
                      const int32_t* nc = nullptr);

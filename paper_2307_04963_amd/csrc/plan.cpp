@@ -468,9 +468,28 @@ struct Run {
   // Partition the rows by flag at decision d.  Sync mode waits for the two
   // counts (the only device->host read); device mode leaves them in
   // d_counts and returns the rows of each branch as bounded by `r`.
-  void compact(Rows r, int d, int32_t* org0, Rows& ones, Rows& zeros) {
+  // `carry`: pairs of tensors whose rows on the zeros' side are to move; true
+  // says that the same launch has moved them.
+  bool compact(Rows r, int d, int32_t* org0, Rows& ones, Rows& zeros,
+               const std::vector<std::pair<int, int>>* carry = nullptr) {
     int32_t* cnt = p->d_counts + 2 * d;
-    launch(P_COMPACT, 0, r.n * (1.0 + 4.0 + 16.0), [&] {
+    k::MoveSet set{};
+    double moved_bytes = 0;
+    if (carry && carry->size() <= 4) {
+      for (const auto& c : *carry) {
+        const size_t rb = p->spec.tensors[c.first].row_bytes(p->spec.dt);
+        set.src[set.count] = tp[c.first];
+        set.dst[set.count] = tp[c.second];
+        set.vpr[set.count++] = rb / 16;
+        moved_bytes += 2.0 * rb * r.n;
+      }
+    }
+    const bool moved = set.count > 0 && k::compact_move_fits(r.n, set);
+    launch(P_COMPACT, 0, r.n * (1.0 + 4.0 + 16.0) + (moved ? moved_bytes : 0.0), [&] {
+      if (moved) {
+        k::compact_move(p->d_flags, orig, r.n, p->d_idx1, p->d_org1, p->d_idx0, org0, cnt, set, s, r.nc);
+        return;
+      }
       if (r.n <= 16384)
         k::compact(p->d_flags, orig, r.n, p->d_idx1, p->d_org1, p->d_idx0, org0, cnt, s, r.nc);
       else
@@ -479,13 +498,14 @@ struct Run {
     if (device) {
       ones = {r.n, cnt, expected(2 * d, r.n)};
       zeros = {r.n, cnt + 1, expected(2 * d + 1, r.n)};
-      return;
+      return moved;
     }
     hip_check(hipMemcpyAsync(p->h_counts + 2 * d, cnt, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s),
               "count readback");
     hip_check(hipStreamSynchronize(s), "count readback sync");
     ones = {p->h_counts[2 * d], nullptr, p->h_counts[2 * d]};
     zeros = {p->h_counts[2 * d + 1], nullptr, p->h_counts[2 * d + 1]};
+    return moved;
   }
 
   // expected count of branch i: an earlier run's, scaled to this batch,
@@ -780,7 +800,8 @@ struct Run {
             launch(P_HEAD, 2.0 * n * nd.hc * nd.ncls, esz * n * HW * nd.hc + 4.0 * nd.ncls * (nd.hc + 1), [&] {
               k::exit_head(tp[nd.src], sp.dt == DType::BF16, n, HW, nd.hc, f32(nd.h_w), f32(nd.h_b),
                            nd.ncls, f32(nd.h_T), nd.tau, nd.final_ ? 1 : 0, nd.index, orig, p->d_flags, logits,
-                           sp.n_out, rec, s, rows.nc, rows.hint);
+                           sp.n_out, rec, s, rows.nc, rows.hint,
+                           nd.final_ && device ? p->d_counts + 2 * nd.decision : nullptr);
             });
           } else if (sp.dt == DType::BF16 && nd.gap_pool && gap_tensor == nd.src) {
             // the producing conv left 32-row chunk sums of this tensor
@@ -812,9 +833,9 @@ struct Run {
             });
           }
           if (nd.final_) {
-            if (device) {
+            if (device && !nd.fused) {
               launch(P_MISC, 0, 8.0, [&] { k::final_counts(rows.nc, n, p->d_counts + 2 * nd.decision, s); });
-            } else {
+            } else if (!device) {
               p->h_counts[2 * nd.decision] = n;
               p->h_counts[2 * nd.decision + 1] = 0;
             }
@@ -823,8 +844,7 @@ struct Run {
           }
           int32_t* next = p->d_orig[orig_next];
           Rows gone, stay;
-          compact(rows, nd.decision, next, gone, stay);
-          move_pairs(nd.pairs, nullptr, p->d_idx0, stay);
+          if (!compact(rows, nd.decision, next, gone, stay, &nd.pairs)) move_pairs(nd.pairs, nullptr, p->d_idx0, stay);
           orig = next;
           orig_next ^= 1;
           rows = stay;
