@@ -1237,7 +1237,14 @@ void dispatch_uni(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
 
 // lanes with taps and sources of their own: 64 x 64, 128 x 64 or 128 x 32 tiles
 template <int KS>
-void dispatch_lanes(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
+void dispatch_lanes(const LdsCfg& c, const ConvP& p, hipStream_t s, int S, bool lean) {
+  if constexpr (KS != 7) {
+    if (c.ns == 1) {
+      if (c.bn == 32) lean ? go_lds<128, 32, 4, 1, KS, 1, true, false>(p, s, S) : go_lds<128, 32, 4, 1, KS, 1, false, false>(p, s, S);
+      else lean ? go_lds<128, 64, 2, 2, KS, 1, true, false>(p, s, S) : go_lds<128, 64, 2, 2, KS, 1, false, false>(p, s, S);
+      return;
+    }
+  }
   if (c.bn == 32) go_lds<128, 32, 4, 1, KS, 3, false, false>(p, s, S);
   else if (c.bm == 64) go_lds<64, 64, 2, 2, KS, 4, false, false>(p, s, S);
   else go_lds<128, 64, 2, 2, KS, 3, false, false>(p, s, S);
@@ -1245,8 +1252,8 @@ void dispatch_lanes(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
 
 void dispatch_lds(int k, const LdsCfg& c, const ConvP& p, hipStream_t s, int S, bool uni) {
   const bool lean = S == 1 && !p.out_f32 && !p.rrows && !p.drows && (p.act == ACT_RELU || p.act == ACT_NONE);
-  if (k == 7) dispatch_lanes<7>(c, p, s, S);
-  else if (!uni) k == 1 ? dispatch_lanes<1>(c, p, s, S) : dispatch_lanes<3>(c, p, s, S);
+  if (k == 7) dispatch_lanes<7>(c, p, s, S, lean);
+  else if (!uni) k == 1 ? dispatch_lanes<1>(c, p, s, S, lean) : dispatch_lanes<3>(c, p, s, S, lean);
   else if (lean) k == 1 ? dispatch_uni<1, true>(c, p, s, S) : dispatch_uni<3, true>(c, p, s, S);
   else k == 1 ? dispatch_uni<1, false>(c, p, s, S) : dispatch_uni<3, false>(c, p, s, S);
 }
@@ -1509,7 +1516,17 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
                : a.cout % 128 == 0 && S * t128 >= 256 ? LdsCfg{128, 128, 2}
                : a.cout % 128 == 0                    ? LdsCfg{64, 128, 3}
                                                       : LdsCfg{128, 64, 3};
-    if (!uni && c.bn > 64) c = {c.bm, 64, 3};
+    // lanes with taps of their own: one K step on at least 256 tiles, or up to
+    // three on 1024, are memory-bound and take one stage (us, three stages | one,
+    // with stride 2: 2048 images of 32x32, 1x1 16 -> 32 31.0 | 18.9, 3x3 16 -> 32
+    // 20.4 | 15.1; of 16x16, 1x1 32 -> 64 15.0 | 12.4, but 3x3 32 -> 64, five
+    // steps, 20.9 | 22.5; 300 images (600 tiles) 1x1 16 -> 32 11.8 | 9.3, but 3x3
+    // 16 -> 32 9.5 | 10.0)
+    if (!uni) {
+      if (!split && a.k != 7 && a.Ho * a.Wo > 1 && t12864 >= (p.Kp == 64 ? 256 : 1024) && p.Kp <= 192)
+        c = {128, a.cout < 64 ? 32 : 64, 1};
+      else if (c.bn > 64 || c.ns == 1) c = {c.bm, 64, 3};
+    }
     p.mt = (p.M + c.bm - 1) / c.bm;
     p.nt = (a.cout + c.bn - 1) / c.bn;
     if (split) {

@@ -29,6 +29,12 @@ CASES = [
     (301, 1, 1, 96, 64, 1, 1, 0, False, 1),        # 64 does not divide the channels
     (5, 9, 9, 32, 96, 3, 2, 1, True, 1),
     (7, 11, 11, 8, 40, 3, 2, 1, False, 2),         # 128 x 32 tiles, K = 72
+    (521, 31, 32, 16, 32, 1, 2, 0, False, 1),      # ... and one stage: 128 x 32 tiles, one K step
+    (521, 31, 32, 16, 24, 3, 2, 1, True, 1),       # three K steps, a ragged channel tile
+    (521, 31, 32, 16, 32, 3, 2, 1, True, 2),       # GELU
+    (521, 31, 32, 32, 64, 1, 2, 0, True, 0),       # 128 x 64 tiles
+    (521, 31, 32, 16, 72, 3, 2, 1, False, 2),
+    (521, 31, 32, 32, 64, 3, 2, 1, False, 1),      # five K steps: three stages
     (3, 7, 9, 16, 64, 7, 1, 3, False, 1),          # 7x7
     (60, 4, 4, 512, 512, 3, 1, 1, True, 1),        # K split on few images: 64 x 128 tiles
     (9, 8, 8, 512, 320, 3, 2, 1, False, 1),        # K split, 64-channel tiles
