@@ -119,22 +119,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
     const int img = quot(m, p.dHW), rem = m - img * HW, r = quot(rem, p.dW);
     return (img * (p.H + 1) + r + 1) * PW + (rem - r * p.W) + 1;
   };
-  const int img0 = quot(m0, p.dHW);
   const int vf = vidx(m0);                        // index of the tile's first pixel
   const int NP = vidx(min(m0 + BM, M) - 1) - vf + 2 * PW + 3;
-  // byte offset of each of this thread's patch slots from the tile's first
-  // image; zero pixels get one that no buffer reaches
+  // byte offset of each of this thread's patch slots; zero pixels get one that
+  // no buffer reaches.  The buffer starts at the first pixel that the patch can
+  // hold (the one above and to the left of the tile's first), so the offsets
+  // span the patch and not the images that it lies in: those may be of any size.
+  const int mp = max(m0 - p.W - 1, 0);
   uint32_t pofs[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int v = vf - PW - 1 + j * 32 + lrow;
     const int vr = quot(v, p.dPW), c = v - vr * PW, img = quot(vr, p.dH1), r = vr - img * (p.H + 1);
     pofs[j] = (c >= 1 && r >= 1 && img < n)
-                  ? static_cast<uint32_t>(((img - img0) * HW + (r - 1) * p.W + (c - 1)) * cin * 2 + lch * 16)
+                  ? static_cast<uint32_t>((img * HW + (r - 1) * p.W + (c - 1) - mp) * cin * 2 + lch * 16)
                   : 0xC0000000u;
   }
-  const uint16_t* const sbase = p.src + static_cast<size_t>(img0) * HW * cin;
-  const size_t sleft = static_cast<size_t>(n - img0) * HW * cin * 2;
+  const uint16_t* const sbase = p.src + static_cast<size_t>(mp) * cin;
+  const size_t sleft = static_cast<size_t>(M - mp) * cin * 2;
   const uint32_t sbytes = sleft < 0x7fffffffu ? static_cast<uint32_t>(sleft) : 0x7fffffffu;
   auto issue_patch = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
