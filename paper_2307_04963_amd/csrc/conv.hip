@@ -345,8 +345,8 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
   int a_pix[JA], a_pix2[JA], a_ih[JA], a_iw[JA];
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
-    // (a 1x1 layer has no padding: there the last row stands in for rows
-    // past M, whose sums are not stored)
+    // (a 1x1 layer on scalar addresses has no padding: there the last row
+    // stands in for rows past M, whose sums are not stored)
     const int m = UNI && KS == 1 ? min(m0 + rbase + j * (NT / 8), M - 1) : m0 + rbase + j * (NT / 8);
     if (m < M) {
       const int img = m / HoWo;
@@ -1502,11 +1502,13 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
     const long t12864 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 63) / 64);
     const bool one = !split && a.cout >= 64 && a.Ho * a.Wo > 1 && t12864 >= 1024 && (a.k != 1 || p.Kp <= 1024);
     // scalar taps and offsets (UNI): 64 divides the channels of each input
-    // tensor, and the tensors lie below 2^31 bytes
+    // tensor, the tensors lie below 2^31 bytes, and a 1x1 layer has no padding
+    // (a specification may ask for it; that path reads every pixel unchecked)
     const long b1 = static_cast<long>(a.src_rows ? a.list_rows : a.n) * a.H * a.W * a.cin1 * 2;
     const long b2 = a.src2 ? static_cast<long>(a.src2_rows ? a.src2_list_rows : a.n) * p.H2 * p.W2 * a.cin2 * 2 : 0;
-    const bool uni = a.k != 7 && a.cin1 % 64 == 0 && (!a.src2 || a.cin2 % 64 == 0) && b1 < 0x7fffffffL &&
-                     b2 < 0x7fffffffL && (!a.src_rows || a.list_rows > 0) && (!a.src2_rows || a.src2_list_rows > 0);
+    const bool uni = (a.k == 3 || (a.k == 1 && a.pad == 0)) && a.cin1 % 64 == 0 && (!a.src2 || a.cin2 % 64 == 0) &&
+                     b1 < 0x7fffffffL && b2 < 0x7fffffffL && (!a.src_rows || a.list_rows > 0) &&
+                     (!a.src2_rows || a.src2_list_rows > 0);
     p.src_bytes = static_cast<uint32_t>(b1);
     // a split layer: 64 x 64 or 64 x 128 tiles while the four ranges of 128 x
     // 128 tiles leave CUs idle (60 images of 4x4x512: 17 us against 24; 255

@@ -142,3 +142,54 @@ def test_folded_projection_with_zero_scales(stride, tiny):
     # one bf16 rounding of y (or of p) may flip between accumulation orders
     assert np.abs(got - ref).max() <= 1e-3 * max(1.0, np.abs(ref).max()), np.abs(got - ref).max()
     plan.close()
+
+
+@pytest.mark.parametrize("cin,k,stride,pad,concat", [
+    (64, 1, 1, 1, False), (128, 1, 2, 1, False), (64, 1, 1, 1, True), (24, 1, 1, 1, False), (64, 3, 1, 3, False),
+    (64, 3, 2, 2, False), (64, 3, 1, 0, False)])
+def test_padding_that_is_not_half_the_kernel(cin, k, stride, pad, concat):
+    # a specification takes any padding up to the kernel's size: a border of
+    # outputs whose window lies outside the image, for a 1x1 layer the shift
+    # alone (44 % of these outputs; the image's pixels are far from zero)
+    import torch
+    from paper_2307_04963_amd import runtime
+    rng = np.random.default_rng(cin + 10 * k + pad + stride)
+    B, HW, cout, ncls = 5, 6, 64, 10
+    blob, man = bytearray(), {}
+
+    def add(name, arr, dt):
+        blob.extend(b"\0" * ((-len(blob)) % 256))
+        man[name] = len(blob)
+        blob.extend(to_bf16_bits(arr).tobytes() if dt == "bf16" else np.asarray(arr, np.float32).tobytes())
+
+    w0 = q(rng.uniform(-0.3, 0.3, (cin, 1, 1, 64)))
+    w = q(rng.uniform(-0.2, 0.2, (cout, k, k, 2 * cin if concat else cin)))
+    a, b = rng.uniform(0.5, 1.5, cout).astype(np.float32), rng.uniform(-0.2, 0.2, cout).astype(np.float32)
+    hw, hb = rng.uniform(-1, 1, (ncls, cout)).astype(np.float32), rng.uniform(-1, 1, ncls).astype(np.float32)
+    for name, arr, dt in (("w0", w0, "bf16"), ("w", w, "bf16"), ("a", a, "f32"), ("b", b, "f32"), ("hw", hw, "f32"),
+                          ("hb", hb, "f32")):
+        add(name, arr, dt)
+    spec = {"version": 1, "dtype": "bf16", "input": {"name": "x", "shape": [HW, HW, 64]}, "n_out": ncls,
+            "nodes": [{"op": "conv", "src": "x", "dst": "h", "k": 1, "cout": cin, "act": "none", "w": {"off": man["w0"]}},
+                      {"op": "conv", "src": "h", "dst": "y", "k": k, "stride": stride, "pad": pad, "cout": cout,
+                       "act": "relu", "w": {"off": man["w"]}, "scale": man["a"], "shift": man["b"],
+                       **({"src2": "h"} if concat else {})},
+                      {"op": "exit", "src": "y", "w": man["hw"], "b": man["hb"], "ncls": ncls, "index": 0,
+                       "final": True}]}
+    plan = runtime.Plan(json.dumps(spec), bytes(blob), 8)
+    x = q(rng.standard_normal((B, HW, HW, 64)) + 2.0)
+    xt = torch.from_numpy(to_bf16_bits(x.astype(np.float32)).view(np.int16).copy()).view(torch.bfloat16).cuda()
+    logits = torch.zeros((B, ncls), device="cuda")
+    rec = torch.zeros((B, 4), dtype=torch.int32, device="cuda")
+    plan.run(xt, None, logits, rec)
+    torch.cuda.synchronize()
+    got = logits.cpu().numpy()
+    ref = []
+    for i in range(B):
+        h = q(conv(x[i], w0, 1, 0))
+        y = q(np.maximum(conv(np.concatenate([h, h], 2) if concat else h, w, stride, pad) * a + b, 0.0))
+        ref.append(hw.astype(np.float64) @ y.reshape(-1, cout).mean(0) + hb)
+    ref = np.stack(ref)
+    # one bf16 rounding of h or y may flip between accumulation orders
+    assert np.abs(got - ref).max() <= 1e-3 * max(1.0, np.abs(ref).max()), np.abs(got - ref).max()
+    plan.close()
