@@ -433,7 +433,8 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
       const int kh = tap / KS, kw = tap - (tap / KS) * KS;
       const int ih = a_ih[j] + kh, iw = a_iw[j] + kw;
       const bool ok = kidx < p.K && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W;
-      const bool second = ci >= p.cin1;
+      // (only a 1x1 layer has a second source)
+      const bool second = KS == 1 && ci >= p.cin1;
       const uint16_t* const g = (second ? p.src2 : p.src) +
                                 (size_t)((second ? a_pix2[j] : a_pix[j]) + kh * p.W + kw) * (second ? p.cin2 : p.cin1) +
                                 (second ? ci - p.cin1 : ci);
@@ -1176,35 +1177,62 @@ struct LdsCfg {
   int bm, bn, ns;
 };
 
-// One LDS stage, the K steps in turn, where the number of workgroups that a CU
-// holds bounds the layer: a spatial layer with at least 1024 tiles of 128 x 64
-// (and K <= 1024 when it is a 1x1 layer).  Measured there (us, 128 x 64 | 128 x
-// 128 | 128 x 256, before: 128 x 64 or 128 x 256 with a wait for the stores of
-// a row before the next): 256 images of 56x56, 64 -> 256 with a residual 183 |
-// 166 | 167, before 175; 182 of 28x28, 128 -> 512 with one 77 | 66 | 74, 80;
-// 182 of 56x56, 256 -> 128 94 | 87, 100; 107 of 14x14, 256 -> 1024 34 | 28 |
-// 33, 37; 529 of 16x16, 128 -> 256, strided 3x3 30 | 27 | 33, 36; 300 of 14x14,
-// 1024 -> 256 56 | 51 | 46, 60.  The other layers are bound by their chains of
-// K steps and by the operand bytes per step.  Measured (us, tile and stages):
-//   20972 rows x 256, K 1024 (164 tiles of 128 x 256): 128 x 256, three stages
-//     18.4; 128 x 128 19.1; 64 x 128 20.9.  20972 x 256, K 2304, strided 3x3:
-//     32.3, 36.4, 37.3
-//   4096 x 1024, K 2048 (256 tiles of 128 x 128): 128 x 128, three stages (one
-//     workgroup per CU) 21.7, two 28.4; 64 x 128 24.6
-//   2499 x 512, K 2048 (160 tiles of 64 x 128): 64 x 128 14.2; 64 x 64 14.7;
-//     128 x 128 18.5.  4080 x 512, K 2304 (256): 16.7, 17.6, 23.6
-//   1024 x 1024, K 2048 (128 tiles of 64 x 128): 64 x 64, four stages 11.5;
-//     64 x 128 14.6.  3136 x 256, K 1024: 7.8, 9.2
-LdsCfg choose_lds(int M, int cout, int Kp, int k, bool one) {
+// The tile rule.  t is the number of 128 x 64 tiles; times in us, measured in
+// turn on one card, on both sides of each line.
+//
+// One stage, the K steps in turn: spatial layers from 1024 tiles on (four
+// workgroups for every CU), whose number hides the loads, except where a 1x1
+// layer's K is deep.  256 images of 56x56, 64 -> 256 with a residual: 128 x 64 |
+// 128 x 128 | 128 x 256 183 | 166 | 167; 182 of 28x28, 128 -> 512 with one 77 | 66 |
+// 74.  K of 1024 runs on 128 x 256 or 128 x 128 alike (290 images of 7x7, 1024 ->
+// 1024: 33 | 38; 300 of 14x14, 1024 -> 256 37 | 41; 137 of 14x14, 1024 -> 1024 65 |
+// 64; 96 of 46x46, 1024 -> 2048, stride 2 256 | 234).
+//
+// Fewer tiles are bound by their chains of K steps and the operand bytes per
+// step.  Scalar addresses (uni):
+//  * 128 x 256, three stages, from 160 of them: 20972 rows x 256, K 1024 (164):
+//    18.4, 128 x 128 on three 19.1, 64 x 128 20.9; 3x3, stride 2, K 2304: 32.3,
+//    36.4, 37.3.  (The gain over 128 x 128 needs the input in the caches, as a
+//    layer's output is for the next one.)
+//  * 128 x 128 from 192: three stages up to one workgroup per CU, then two, two
+//    per CU (4096 x 1024, K 2048, 256 tiles: 21.7, two stages 28.4, 64 x 128
+//    24.6).  64 x 128 from 160: 2499 x 512, K 2048: 14.2, 64 x 64 14.7; 1024 x
+//    1024, K 2048, 128 tiles: 14.6, 64 x 64 11.5.
+// Addresses per lane take more instructions per step and tiles of their own: 256
+// images of 28x28, 480 -> 256: 128 x 128 on one stage 90 (128 x 64 on three 125);
+// 64 x 128 on three stages while two workgroups per CU hold them all, else on two,
+// three per CU (124 of 22x22, 1000 -> 320, stride 2, 705 tiles: 21.4, three 22.3,
+// 64 x 64 28.2; 9 of 32x32, 64 -> 1024, 7x7, stride 2, 288: three 32.0, two 39.7);
+// 64 x 64 where half of a 64 x 128 tile can be empty (875 of 7x7, 480 -> 192,
+// stride 2: 9.8, 64 x 128 9.8, 128 x 64 on three 10.9).
+// Below 64 channels they take two stages where there are more tiles than three
+// (60 KB, two workgroups per CU) hold, unless the K is deep (568 images of 28x28,
+// 240 -> 32: 41, three 45; 149 of 32x32, 600 -> 32: 40.0, three 34.4), and one for
+// one K step from 256 tiles, or three from 1024 (2048 images of 32x32, stride 2, 16
+// -> 32: 1x1 18.9, three 31.0, 3x3 15.1, 20.4).
+LdsCfg choose_lds(int M, int cout, int Kp, int k, bool spatial, bool uni) {
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((cout + bn - 1) / bn); };
-  if (cout < 64) return {128, 32, 3};
-  if (one) return cout % 256 == 0 && k == 1 && Kp >= 1024 ? LdsCfg{128, 256, 1} : cout % 128 == 0 ? LdsCfg{128, 128, 1} : LdsCfg{128, 64, 1};
+  const long t = tiles(128, 64);
+  const bool n128 = cout % 128 == 0;
+  if (cout < 64) {
+    if (!uni && Kp <= 192 && t >= (Kp == 64 ? 256 : 1024)) return {128, 32, 1};
+    return {128, 32, !uni && tiles(128, 32) > 512 && Kp <= 512 ? 2 : 3};
+  }
+  if (t >= 1024 && (!uni || (spatial && (k != 1 || Kp <= 1024))))
+    return uni && k == 1 && cout % 256 == 0 && Kp == 1024 ? LdsCfg{128, 256, 1} : LdsCfg{128, n128 ? 128 : 64, 1};
+  if (!uni) {
+    const long n = tiles(64, 128);
+    const bool whole = n128 || (cout > 64 && Kp > 512 && t >= 256 && (n <= 512 || t >= 512));
+    if (whole && n >= 160) return {64, 128, n <= 512 ? 3 : 2};
+    if (t >= 512) return {128, 64, 1};
+    return {64, 64, t >= 256 ? 2 : 4};
+  }
   if (cout % 256 == 0 && tiles(128, 256) >= 160) return {128, 256, 3};
-  if (cout % 128 == 0) {
-    const long t = tiles(128, 128);
-    if (t >= 192) return {128, 128, t <= 256 ? 3 : 2};
+  if (n128) {
+    const long t128 = tiles(128, 128);
+    if (t128 >= 192) return {128, 128, t128 <= 256 ? 3 : 2};
     if (tiles(64, 128) >= 160) return {64, 128, 3};
-  } else if (tiles(128, 64) >= 256) {
+  } else if (t >= 256) {
     return {128, 64, 3};
   }
   return {64, 64, 4};
@@ -1213,49 +1241,44 @@ LdsCfg choose_lds(int M, int cout, int Kp, int k, bool one) {
 // LEAN: ReLU or no activation, bf16 output in the layer's own rows, no K split
 // (fewer registers, and stores and residual through range-checked buffers).
 // UNI: scalar taps and sources (below).
-template <int BM, int BN, int WM, int WN, int KS, int NS, bool LEAN, bool UNI = true>
+template <int BM, int BN, int WM, int WN, int KS, int NS, bool LEAN, bool UNI>
 void go_lds(const ConvP& p, hipStream_t s, int S) {
   hipLaunchKernelGGL((conv_lds_kernel<BM, BN, WM, WN, KS, NS, LEAN, UNI>), dim3(p.mt * p.nt * S), dim3(64 * WM * WN), 0,
                      s, p);
 }
 
-template <int KS, bool LEAN>
-void dispatch_uni(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
+template <int KS, bool LEAN, bool UNI>
+void dispatch_tile(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
   switch ((c.bm * 1000 + c.bn) * 10 + c.ns) {
-    case 1281281: go_lds<128, 128, 2, 2, KS, 1, LEAN>(p, s, S); break;
-    case 1281282: go_lds<128, 128, 2, 2, KS, 2, LEAN>(p, s, S); break;
-    case 1281283: go_lds<128, 128, 2, 2, KS, 3, LEAN>(p, s, S); break;
-    case 1280641: go_lds<128, 64, 2, 2, KS, 1, LEAN>(p, s, S); break;
-    case 1280643: go_lds<128, 64, 2, 2, KS, 3, LEAN>(p, s, S); break;
-    case 1282561: go_lds<128, 256, 2, 4, KS, 1, LEAN>(p, s, S); break;
-    case 1282563: go_lds<128, 256, 2, 4, KS, 3, LEAN>(p, s, S); break;
-    case 641283: go_lds<64, 128, 2, 2, KS, 3, LEAN>(p, s, S); break;
-    case 640644: go_lds<64, 64, 2, 2, KS, 4, LEAN>(p, s, S); break;
-    default: go_lds<128, 32, 4, 1, KS, 3, LEAN>(p, s, S); break;
+    case 1281281: return go_lds<128, 128, 2, 2, KS, 1, LEAN, UNI>(p, s, S);
+    case 1280641: return go_lds<128, 64, 2, 2, KS, 1, LEAN, UNI>(p, s, S);
+    case 641283: return go_lds<64, 128, 2, 2, KS, 3, LEAN, UNI>(p, s, S);
+    case 640644: return go_lds<64, 64, 2, 2, KS, 4, LEAN, UNI>(p, s, S);
+    case 1280323: return go_lds<128, 32, 4, 1, KS, 3, LEAN, UNI>(p, s, S);
   }
-}
-
-// lanes with taps and sources of their own: 64 x 64, 128 x 64 or 128 x 32 tiles
-template <int KS>
-void dispatch_lanes(const LdsCfg& c, const ConvP& p, hipStream_t s, int S, bool lean) {
-  if constexpr (KS != 7) {
-    if (c.ns == 1) {
-      if (c.bn == 32) lean ? go_lds<128, 32, 4, 1, KS, 1, true, false>(p, s, S) : go_lds<128, 32, 4, 1, KS, 1, false, false>(p, s, S);
-      else lean ? go_lds<128, 64, 2, 2, KS, 1, true, false>(p, s, S) : go_lds<128, 64, 2, 2, KS, 1, false, false>(p, s, S);
-      return;
-    }
+  if constexpr (UNI) {
+    if (c.bm == 128 && c.bn == 256 && c.ns == 3) return go_lds<128, 256, 2, 4, KS, 3, LEAN, true>(p, s, S);
+    if (c.bm == 128 && c.bn == 128 && c.ns == 2) return go_lds<128, 128, 2, 2, KS, 2, LEAN, true>(p, s, S);
+    if (c.bm == 128 && c.bn == 128 && c.ns == 3) return go_lds<128, 128, 2, 2, KS, 3, LEAN, true>(p, s, S);
+    if (c.bm == 128 && c.bn == 64 && c.ns == 3) return go_lds<128, 64, 2, 2, KS, 3, LEAN, true>(p, s, S);
+    if constexpr (KS == 1)
+      if (c.bm == 128 && c.bn == 256 && c.ns == 1) return go_lds<128, 256, 2, 4, KS, 1, LEAN, true>(p, s, S);
+  } else {
+    if (c.bm == 64 && c.bn == 128 && c.ns == 2) return go_lds<64, 128, 2, 2, KS, 2, LEAN, false>(p, s, S);
+    if (c.bm == 64 && c.bn == 64 && c.ns == 2) return go_lds<64, 64, 2, 2, KS, 2, LEAN, false>(p, s, S);
+    if (c.bm == 128 && c.bn == 32 && c.ns == 1) return go_lds<128, 32, 4, 1, KS, 1, LEAN, false>(p, s, S);
+    if (c.bm == 128 && c.bn == 32 && c.ns == 2) return go_lds<128, 32, 4, 1, KS, 2, LEAN, false>(p, s, S);
   }
-  if (c.bn == 32) go_lds<128, 32, 4, 1, KS, 3, false, false>(p, s, S);
-  else if (c.bm == 64) go_lds<64, 64, 2, 2, KS, 4, false, false>(p, s, S);
-  else go_lds<128, 64, 2, 2, KS, 3, false, false>(p, s, S);
+  throw std::invalid_argument("conv_bf16: no kernel for this tile");   // (the grid is laid out for the tile)
 }
 
 void dispatch_lds(int k, const LdsCfg& c, const ConvP& p, hipStream_t s, int S, bool uni) {
   const bool lean = S == 1 && !p.out_f32 && !p.rrows && !p.drows && (p.act == ACT_RELU || p.act == ACT_NONE);
-  if (k == 7) dispatch_lanes<7>(c, p, s, S, lean);
-  else if (!uni) k == 1 ? dispatch_lanes<1>(c, p, s, S, lean) : dispatch_lanes<3>(c, p, s, S, lean);
-  else if (lean) k == 1 ? dispatch_uni<1, true>(c, p, s, S) : dispatch_uni<3, true>(c, p, s, S);
-  else k == 1 ? dispatch_uni<1, false>(c, p, s, S) : dispatch_uni<3, false>(c, p, s, S);
+  if (k == 7) dispatch_tile<7, false, false>(c, p, s, S);
+  else if (uni && lean) k == 1 ? dispatch_tile<1, true, true>(c, p, s, S) : dispatch_tile<3, true, true>(c, p, s, S);
+  else if (uni) k == 1 ? dispatch_tile<1, false, true>(c, p, s, S) : dispatch_tile<3, false, true>(c, p, s, S);
+  else if (lean) k == 1 ? dispatch_tile<1, true, false>(c, p, s, S) : dispatch_tile<3, true, false>(c, p, s, S);
+  else k == 1 ? dispatch_tile<1, false, false>(c, p, s, S) : dispatch_tile<3, false, false>(c, p, s, S);
 }
 
 // Tile geometry of the halo kernels: BM-pixel tiles of R whole rows of one
@@ -1478,9 +1501,8 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
   // the direct-to-LDS kernel stores 8 channels per 16-byte vector
   const bool vec_out = a.cout % 8 == 0 && (reinterpret_cast<uintptr_t>(a.dst) & 15) == 0 &&
                        (reinterpret_cast<uintptr_t>(a.res) & 15) == 0 && a.zeros != nullptr;
-  // the streamed-weight halo kernel stages whole images from contiguous
-  // rows: a layer with row lists takes the register-weight halo kernel
-  // (image mode) or the implicit GEMM
+  // the kernel on linear pixel tiles reads contiguous images: a layer with row
+  // lists takes the register-weight halo kernel (image mode) or the implicit GEMM
   const bool listed = a.src_rows || a.src2_rows || a.res_rows || a.dst_rows;
   if (conv3_narrow(a, s)) return false;   // 16 / 32 channels: row lists allowed
   // 64 -> 64 channels on few pixels: the tile kernel, whose workgroups start
@@ -1497,10 +1519,6 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
     const int S = conv_ksplit(a.Ho, a.Wo, a.cout, p.K, a.out_f32 != 0);
     const bool split = S > 1 && a.splitws && !a.res_rows && !a.dst_rows && !a.kfold && !special &&
                        a.splitws_bytes >= static_cast<size_t>(S) * p.M * a.cout * sizeof(float);
-    // one LDS stage: a spatial layer with at least 1024 tiles of 128 x 64 (and
-    // K <= 1024 for a 1x1 layer)
-    const long t12864 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 63) / 64);
-    const bool one = !split && a.cout >= 64 && a.Ho * a.Wo > 1 && t12864 >= 1024 && (a.k != 1 || p.Kp <= 1024);
     // scalar taps and offsets (UNI): 64 divides the channels of each input
     // tensor, the tensors lie below 2^31 bytes, and a 1x1 layer has no padding
     // (a specification may ask for it; that path reads every pixel unchecked)
@@ -1510,25 +1528,19 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
                      b1 < 0x7fffffffL && b2 < 0x7fffffffL && (!a.src_rows || a.list_rows > 0) &&
                      (!a.src2_rows || a.src2_list_rows > 0);
     p.src_bytes = static_cast<uint32_t>(b1);
-    // a split layer: 64 x 64 or 64 x 128 tiles while the four ranges of 128 x
-    // 128 tiles leave CUs idle (60 images of 4x4x512: 17 us against 24; 255
-    // images, 512 workgroups of 128 x 128: 39 against 42)
+    // a split layer: 64 x 128 tiles while the four ranges of 128 x 128 tiles
+    // leave CUs idle (60 images of 4x4x512: 17 us against 24; 255 images, 512
+    // workgroups of 128 x 128: 39 against 42); addresses per lane: up to 512 (7x7,
+    // 128 -> 512 on 7x7: 60 images, 368 workgroups, 43, 128 x 128 on one stage 47;
+    // 120 images, 736, 74, 67)
     const long t128 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 127) / 128);
-    LdsCfg c = !split                                 ? choose_lds(Mh, a.cout, p.Kp, a.k, one)
-               : a.cout % 128 == 0 && S * t128 >= 256 ? LdsCfg{128, 128, 2}
-               : a.cout % 128 == 0                    ? LdsCfg{64, 128, 3}
-                                                      : LdsCfg{128, 64, 3};
-    // lanes with taps of their own: one K step on at least 256 tiles, or up to
-    // three on 1024, are memory-bound and take one stage (us, three stages | one,
-    // with stride 2: 2048 images of 32x32, 1x1 16 -> 32 31.0 | 18.9, 3x3 16 -> 32
-    // 20.4 | 15.1; of 16x16, 1x1 32 -> 64 15.0 | 12.4, but 3x3 32 -> 64, five
-    // steps, 20.9 | 22.5; 300 images (600 tiles) 1x1 16 -> 32 11.8 | 9.3, but 3x3
-    // 16 -> 32 9.5 | 10.0)
-    if (!uni) {
-      if (!split && a.k != 7 && a.Ho * a.Wo > 1 && t12864 >= (p.Kp == 64 ? 256 : 1024) && p.Kp <= 192)
-        c = {128, a.cout < 64 ? 32 : 64, 1};
-      else if (c.bn > 64 || c.ns == 1) c = {c.bm, 64, 3};
-    }
+    const bool few = S * t128 < 256;
+    const LdsCfg c = !split         ? choose_lds(Mh, a.cout, p.Kp, a.k, a.Ho * a.Wo > 1, uni)
+                     : a.cout % 128 ? (uni ? LdsCfg{128, 64, 3} : few ? LdsCfg{64, 64, 2} : LdsCfg{128, 64, 1})
+                     : few          ? LdsCfg{64, 128, 3}
+                     : uni          ? LdsCfg{128, 128, 2}
+                     : S * t128 < 512 ? LdsCfg{64, 128, 3}
+                                      : LdsCfg{128, 128, 1};
     p.mt = (p.M + c.bm - 1) / c.bm;
     p.nt = (a.cout + c.bn - 1) / c.bn;
     if (split) {

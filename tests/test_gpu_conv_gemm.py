@@ -38,6 +38,19 @@ CASES = [
     (3, 7, 9, 16, 64, 7, 1, 3, False, 1),          # 7x7
     (60, 4, 4, 512, 512, 3, 1, 1, True, 1),        # K split on few images: 64 x 128 tiles
     (9, 8, 8, 512, 320, 3, 2, 1, False, 1),        # K split, 64-channel tiles
+    # addresses per lane
+    (171, 14, 14, 96, 256, 1, 1, 0, True, 2),      # 128 x 128, one stage
+    (42, 28, 28, 8, 256, 7, 1, 3, False, 1),       # ... 7x7
+    (53, 14, 14, 160, 128, 1, 1, 0, True, 1),      # 64 x 128, three stages
+    (171, 14, 14, 96, 128, 1, 1, 0, False, 0),     # ... two
+    (13, 28, 28, 600, 320, 1, 1, 0, True, 1),      # ... three, a ragged channel tile, K = 600
+    (19, 28, 28, 600, 320, 1, 1, 0, False, 2),     # ... two
+    (85, 14, 14, 96, 96, 1, 1, 0, False, 1),       # 64 x 64, two stages
+    (521, 16, 16, 240, 32, 1, 1, 0, True, 1),      # 128 x 32, two stages
+    (3, 7, 7, 128, 512, 7, 1, 3, False, 1),        # K split: 64 x 128 tiles
+    (90, 7, 7, 128, 512, 7, 1, 3, True, 2),        # ... 128 x 128, one stage
+    (5, 7, 7, 128, 320, 7, 1, 3, False, 0),        # ... 64 x 64
+    (57, 7, 7, 128, 320, 7, 1, 3, True, 1),        # ... 128 x 64
 ]
 
 

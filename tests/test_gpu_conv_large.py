@@ -15,6 +15,8 @@ CASES = [
     # n, H, cin, cout, k, stride; 64 pixels wide, so a row of 128 channels is 2^14 bytes
     (1, 140000, 128, 64, 3, 1),      # one image past 2^31 bytes: the 3x3 kernel on linear pixel tiles
     (2, 131071, 128, 64, 3, 1),      # a tile that starts in an image just below 2^31 bytes and ends in the next
+    (1, 140000, 128, 64, 1, 1),      # the implicit GEMM, with addresses per lane from 2^31 bytes on
+    (1, 140000, 128, 128, 3, 2),
 ]
 
 
