@@ -1205,18 +1205,21 @@ struct LdsCfg {
 // 64 x 64 28.2; 9 of 32x32, 64 -> 1024, 7x7, stride 2, 288: three 32.0, two 39.7);
 // 64 x 64 where half of a 64 x 128 tile can be empty (875 of 7x7, 480 -> 192,
 // stride 2: 9.8, 64 x 128 9.8, 128 x 64 on three 10.9).
-// Below 64 channels they take two stages where there are more tiles than three
-// (60 KB, two workgroups per CU) hold, unless the K is deep (568 images of 28x28,
-// 240 -> 32: 41, three 45; 149 of 32x32, 600 -> 32: 40.0, three 34.4), and one for
-// one K step from 256 tiles, or three from 1024 (2048 images of 32x32, stride 2, 16
-// -> 32: 1x1 18.9, three 31.0, 3x3 15.1, 20.4).
-LdsCfg choose_lds(int M, int cout, int Kp, int k, bool spatial, bool uni) {
+// Below 64 channels: three stages (60 KB, two workgroups per CU), two where there
+// are more tiles than that (1765 images of 56x56, 64 -> 32, stride 2: 64, three
+// 96) unless the K is deep (149 of 32x32, 600 -> 32: 40.0, three 34.4; 1018 of
+// 42x42, 256 -> 16, 3x3: 1075, 588) or the taps of a 3x3 layer do not overlap
+// (1823 of 16x16, 128 -> 16, stride 2: 36.4, 30.5); one for one K step of
+// per-lane addresses from 256 tiles, or three from 1024 (2048 images of 32x32,
+// stride 2, 16 -> 32: 1x1 18.9, three 31.0, 3x3 15.1, 20.4).
+LdsCfg choose_lds(int M, int cout, int Kp, int k, int stride, bool spatial, bool uni) {
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((cout + bn - 1) / bn); };
   const long t = tiles(128, 64);
   const bool n128 = cout % 128 == 0;
   if (cout < 64) {
     if (!uni && Kp <= 192 && t >= (Kp == 64 ? 256 : 1024)) return {128, 32, 1};
-    return {128, 32, !uni && tiles(128, 32) > 512 && Kp <= 512 ? 2 : 3};
+    const bool shallow = !uni ? Kp <= 512 : k == 1 || (stride == 1 && Kp <= 1152);
+    return {128, 32, tiles(128, 32) > 512 && shallow ? 2 : 3};
   }
   if (t >= 1024 && (!uni || (spatial && (k != 1 || Kp <= 1024))))
     return uni && k == 1 && cout % 256 == 0 && Kp == 1024 ? LdsCfg{128, 256, 1} : LdsCfg{128, n128 ? 128 : 64, 1};
@@ -1254,6 +1257,7 @@ void dispatch_tile(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
     case 1280641: return go_lds<128, 64, 2, 2, KS, 1, LEAN, UNI>(p, s, S);
     case 641283: return go_lds<64, 128, 2, 2, KS, 3, LEAN, UNI>(p, s, S);
     case 640644: return go_lds<64, 64, 2, 2, KS, 4, LEAN, UNI>(p, s, S);
+    case 1280322: return go_lds<128, 32, 4, 1, KS, 2, LEAN, UNI>(p, s, S);
     case 1280323: return go_lds<128, 32, 4, 1, KS, 3, LEAN, UNI>(p, s, S);
   }
   if constexpr (UNI) {
@@ -1267,7 +1271,6 @@ void dispatch_tile(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
     if (c.bm == 64 && c.bn == 128 && c.ns == 2) return go_lds<64, 128, 2, 2, KS, 2, LEAN, false>(p, s, S);
     if (c.bm == 64 && c.bn == 64 && c.ns == 2) return go_lds<64, 64, 2, 2, KS, 2, LEAN, false>(p, s, S);
     if (c.bm == 128 && c.bn == 32 && c.ns == 1) return go_lds<128, 32, 4, 1, KS, 1, LEAN, false>(p, s, S);
-    if (c.bm == 128 && c.bn == 32 && c.ns == 2) return go_lds<128, 32, 4, 1, KS, 2, LEAN, false>(p, s, S);
   }
   throw std::invalid_argument("conv_bf16: no kernel for this tile");   // (the grid is laid out for the tile)
 }
@@ -1535,7 +1538,7 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
     // 120 images, 736, 74, 67)
     const long t128 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 127) / 128);
     const bool few = S * t128 < 256;
-    const LdsCfg c = !split         ? choose_lds(Mh, a.cout, p.Kp, a.k, a.Ho * a.Wo > 1, uni)
+    const LdsCfg c = !split         ? choose_lds(Mh, a.cout, p.Kp, a.k, a.stride, a.Ho * a.Wo > 1, uni)
                      : a.cout % 128 ? (uni ? LdsCfg{128, 64, 3} : few ? LdsCfg{64, 64, 2} : LdsCfg{128, 64, 1})
                      : few          ? LdsCfg{64, 128, 3}
                      : uni          ? LdsCfg{128, 128, 2}

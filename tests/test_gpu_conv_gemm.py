@@ -38,6 +38,9 @@ CASES = [
     (3, 7, 9, 16, 64, 7, 1, 3, False, 1),          # 7x7
     (60, 4, 4, 512, 512, 3, 1, 1, True, 1),        # K split on few images: 64 x 128 tiles
     (9, 8, 8, 512, 320, 3, 2, 1, False, 1),        # K split, 64-channel tiles
+    (521, 16, 16, 64, 24, 1, 1, 0, True, 2),       # 128 x 32, two stages
+    (521, 16, 16, 64, 24, 3, 1, 1, False, 1),
+    (521, 31, 32, 64, 24, 3, 2, 1, False, 1),      # ... three: stride 2
     # addresses per lane
     (171, 14, 14, 96, 256, 1, 1, 0, True, 2),      # 128 x 128, one stage
     (42, 28, 28, 8, 256, 7, 1, 3, False, 1),       # ... 7x7
