@@ -732,8 +732,8 @@ __global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS 
   };
   if (p.act == ACT_RELU)
     epilogue(std::integral_constant<int, ACT_RELU>{});
-  else if (!LEAN && p.act == ACT_GELU)
-    epilogue(std::integral_constant<int, LEAN ? ACT_NONE : ACT_GELU>{});
+  else if (p.act == ACT_GELU)
+    epilogue(std::integral_constant<int, ACT_GELU>{});
   else if (!LEAN && p.act == ACT_TANH)
     epilogue(std::integral_constant<int, LEAN ? ACT_NONE : ACT_TANH>{});
   else if (!LEAN && p.act == ACT_LSTM)
@@ -1180,16 +1180,31 @@ struct LdsCfg {
 // The tile rule.  t is the number of 128 x 64 tiles; times in us, measured in
 // turn on one card, on both sides of each line.
 //
-// One stage, the K steps in turn: spatial layers from 1024 tiles on (four
-// workgroups for every CU), whose number hides the loads, except where a 1x1
-// layer's K is deep.  256 images of 56x56, 64 -> 256 with a residual: 128 x 64 |
-// 128 x 128 | 128 x 256 183 | 166 | 167; 182 of 28x28, 128 -> 512 with one 77 | 66 |
-// 74.  K of 1024 runs on 128 x 256 or 128 x 128 alike (290 images of 7x7, 1024 ->
-// 1024: 33 | 38; 300 of 14x14, 1024 -> 256 37 | 41; 137 of 14x14, 1024 -> 1024 65 |
-// 64; 96 of 46x46, 1024 -> 2048, stride 2 256 | 234).
+// One stage, the K steps in turn: from 1024 tiles on (four workgroups for every
+// CU) their number hides the loads, except where a 1x1 layer's K is deep.  256
+// images of 56x56, 64 -> 256 with a residual: 128 x 64 | 128 x 128 | 128 x 256
+// 183 | 166 | 167; 182 of 28x28, 128 -> 512 with one 77 | 66 | 74; 35915 rows,
+// 128 -> 1024, GELU: 128 x 128 on one stage 37, 128 x 256 on three 52; 4096 rows,
+// 1024 -> 2048 (1024 tiles, one round of two stages) 33.8, two 27.1; 2073 rows,
+// 1024 -> 4096 (1088) 31.4, two 37.9.  K of 1024 runs on 128 x 256 or 128 x 128
+// alike (290 images of 7x7, 1024 -> 1024: 33 | 38; 300 of 14x14, 1024 -> 256 37 |
+// 41; 137 of 14x14, 1024 -> 1024 65 | 64; 96 of 46x46, 1024 -> 2048, stride 2 256
+// | 234).
 //
 // Fewer tiles are bound by their chains of K steps and the operand bytes per
 // step.  Scalar addresses (uni):
+//  * 1x1, cout a multiple of 128, short K: two stages of 64 x 64 below 450 tiles
+//    and K <= 256 (3000 rows, 256 -> 1024, GELU: 8.4, 128 x 128 on three 11.2; 264
+//    images of 7x7, 1024 -> 256: 15.9, 12.7), one of 128 x 64 from 450 with K <=
+//    128 (3017 rows, 64 -> 1536, GELU 9.6, 128 x 128 on two 11.4; 20535 rows, 256
+//    -> 384: 11.2, two 10.5).
+//  * 1x1, other cout: two stages of 64 x 64 up to 360 tiles in one column (35
+//    images of 32x32, 768 -> 64: 13.1, 128 x 64 on three 15.5; 51553 rows, 512 ->
+//    64, 403 tiles: 13.4, 12.6), 320 in several (13577 rows, 1024 -> 192, 321
+//    tiles: 14.1, 13.2; 11606, 1536 -> 192, 273: 17.7, 18.5), 450 with short K
+//    (15874 rows, 64 -> 192: 5.7, 6.2); one stage of 128 x 64 from 512 with K <=
+//    512 (5 of 56x56, 256 -> 320: 9.2, three 10.9; 76 of 16x16, 1024 -> 192: 17.1,
+//    three 15.2).
 //  * 128 x 256, three stages, from 160 of them: 20972 rows x 256, K 1024 (164):
 //    18.4, 128 x 128 on three 19.1, 64 x 128 20.9; 3x3, stride 2, K 2304: 32.3,
 //    36.4, 37.3.  (The gain over 128 x 128 needs the input in the caches, as a
@@ -1212,7 +1227,7 @@ struct LdsCfg {
 // (1823 of 16x16, 128 -> 16, stride 2: 36.4, 30.5); one for one K step of
 // per-lane addresses from 256 tiles, or three from 1024 (2048 images of 32x32,
 // stride 2, 16 -> 32: 1x1 18.9, three 31.0, 3x3 15.1, 20.4).
-LdsCfg choose_lds(int M, int cout, int Kp, int k, int stride, bool spatial, bool uni) {
+LdsCfg choose_lds(int M, int cout, int Kp, int k, int stride, bool uni) {
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((cout + bn - 1) / bn); };
   const long t = tiles(128, 64);
   const bool n128 = cout % 128 == 0;
@@ -1221,7 +1236,7 @@ LdsCfg choose_lds(int M, int cout, int Kp, int k, int stride, bool spatial, bool
     const bool shallow = !uni ? Kp <= 512 : k == 1 || (stride == 1 && Kp <= 1152);
     return {128, 32, tiles(128, 32) > 512 && shallow ? 2 : 3};
   }
-  if (t >= 1024 && (!uni || (spatial && (k != 1 || Kp <= 1024))))
+  if (t >= 1024 && (!uni || k != 1 || Kp <= 256 || (t > 1024 && Kp <= 1024)))
     return uni && k == 1 && cout % 256 == 0 && Kp == 1024 ? LdsCfg{128, 256, 1} : LdsCfg{128, n128 ? 128 : 64, 1};
   if (!uni) {
     const long n = tiles(64, 128);
@@ -1229,6 +1244,10 @@ LdsCfg choose_lds(int M, int cout, int Kp, int k, int stride, bool spatial, bool
     if (whole && n >= 160) return {64, 128, n <= 512 ? 3 : 2};
     if (t >= 512) return {128, 64, 1};
     return {64, 64, t >= 256 ? 2 : 4};
+  }
+  if (k == 1 && t >= 256) {
+    if (n128 ? t < 450 && Kp <= 256 : t < (cout == 64 ? 360 : Kp <= 256 ? 450 : 320)) return {64, 64, 2};
+    if (n128 ? t >= 450 && Kp <= 128 : t >= 512 && Kp <= 512) return {128, 64, 1};
   }
   if (cout % 256 == 0 && tiles(128, 256) >= 160) return {128, 256, 3};
   if (n128) {
@@ -1241,9 +1260,9 @@ LdsCfg choose_lds(int M, int cout, int Kp, int k, int stride, bool spatial, bool
   return {64, 64, 4};
 }
 
-// LEAN: ReLU or no activation, bf16 output in the layer's own rows, no K split
-// (fewer registers, and stores and residual through range-checked buffers).
-// UNI: scalar taps and sources (below).
+// LEAN: bf16 output in the layer's own rows, no K split, no cell (fewer
+// registers, and stores and residual through range-checked buffers).  UNI:
+// scalar taps and sources (below).
 template <int BM, int BN, int WM, int WN, int KS, int NS, bool LEAN, bool UNI>
 void go_lds(const ConvP& p, hipStream_t s, int S) {
   hipLaunchKernelGGL((conv_lds_kernel<BM, BN, WM, WN, KS, NS, LEAN, UNI>), dim3(p.mt * p.nt * S), dim3(64 * WM * WN), 0,
@@ -1260,6 +1279,8 @@ void dispatch_tile(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
     case 1280322: return go_lds<128, 32, 4, 1, KS, 2, LEAN, UNI>(p, s, S);
     case 1280323: return go_lds<128, 32, 4, 1, KS, 3, LEAN, UNI>(p, s, S);
   }
+  if constexpr (!UNI || KS == 1)
+    if (c.bm == 64 && c.bn == 64 && c.ns == 2) return go_lds<64, 64, 2, 2, KS, 2, LEAN, UNI>(p, s, S);
   if constexpr (UNI) {
     if (c.bm == 128 && c.bn == 256 && c.ns == 3) return go_lds<128, 256, 2, 4, KS, 3, LEAN, true>(p, s, S);
     if (c.bm == 128 && c.bn == 128 && c.ns == 2) return go_lds<128, 128, 2, 2, KS, 2, LEAN, true>(p, s, S);
@@ -1269,14 +1290,14 @@ void dispatch_tile(const LdsCfg& c, const ConvP& p, hipStream_t s, int S) {
       if (c.bm == 128 && c.bn == 256 && c.ns == 1) return go_lds<128, 256, 2, 4, KS, 1, LEAN, true>(p, s, S);
   } else {
     if (c.bm == 64 && c.bn == 128 && c.ns == 2) return go_lds<64, 128, 2, 2, KS, 2, LEAN, false>(p, s, S);
-    if (c.bm == 64 && c.bn == 64 && c.ns == 2) return go_lds<64, 64, 2, 2, KS, 2, LEAN, false>(p, s, S);
     if (c.bm == 128 && c.bn == 32 && c.ns == 1) return go_lds<128, 32, 4, 1, KS, 1, LEAN, false>(p, s, S);
   }
   throw std::invalid_argument("conv_bf16: no kernel for this tile");   // (the grid is laid out for the tile)
 }
 
 void dispatch_lds(int k, const LdsCfg& c, const ConvP& p, hipStream_t s, int S, bool uni) {
-  const bool lean = S == 1 && !p.out_f32 && !p.rrows && !p.drows && (p.act == ACT_RELU || p.act == ACT_NONE);
+  const bool lean =
+      S == 1 && !p.out_f32 && !p.rrows && !p.drows && (p.act == ACT_RELU || p.act == ACT_NONE || p.act == ACT_GELU);
   if (k == 7) dispatch_tile<7, false, false>(c, p, s, S);
   else if (uni && lean) k == 1 ? dispatch_tile<1, true, true>(c, p, s, S) : dispatch_tile<3, true, true>(c, p, s, S);
   else if (uni) k == 1 ? dispatch_tile<1, false, true>(c, p, s, S) : dispatch_tile<3, false, true>(c, p, s, S);
@@ -1538,7 +1559,7 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
     // 120 images, 736, 74, 67)
     const long t128 = (static_cast<long>(Mh) + 127) / 128 * ((a.cout + 127) / 128);
     const bool few = S * t128 < 256;
-    const LdsCfg c = !split         ? choose_lds(Mh, a.cout, p.Kp, a.k, a.stride, a.Ho * a.Wo > 1, uni)
+    const LdsCfg c = !split         ? choose_lds(Mh, a.cout, p.Kp, a.k, a.stride, uni)
                      : a.cout % 128 ? (uni ? LdsCfg{128, 64, 3} : few ? LdsCfg{64, 64, 2} : LdsCfg{128, 64, 1})
                      : few          ? LdsCfg{64, 128, 3}
                      : uni          ? LdsCfg{128, 128, 2}

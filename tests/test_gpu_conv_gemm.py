@@ -38,6 +38,14 @@ CASES = [
     (3, 7, 9, 16, 64, 7, 1, 3, False, 1),          # 7x7
     (60, 4, 4, 512, 512, 3, 1, 1, True, 1),        # K split on few images: 64 x 128 tiles
     (9, 8, 8, 512, 320, 3, 2, 1, False, 1),        # K split, 64-channel tiles
+    # 1x1 on scalar addresses, one tile column's worth above and below
+    (85, 14, 14, 256, 128, 1, 1, 0, True, 2),      # 64 x 64, two stages: short K
+    (2100, 4, 4, 768, 64, 1, 1, 0, False, 1),      # ... and 64 channels
+    (300, 14, 14, 128, 128, 1, 1, 0, True, 2),     # 128 x 64, one stage: one or two K steps
+    (5, 56, 56, 256, 320, 1, 1, 0, False, 1),      # ... and other channel counts
+    (33001, 1, 1, 128, 256, 1, 1, 0, False, 2),    # linear, 128 x 128 on one stage
+    (301, 14, 14, 1024, 256, 1, 1, 0, True, 1),    # 128 x 256 on one stage, ragged rows
+    (301, 14, 14, 1024, 256, 1, 1, 0, False, 2),
     (521, 16, 16, 64, 24, 1, 1, 0, True, 2),       # 128 x 32, two stages
     (521, 16, 16, 64, 24, 3, 1, 1, False, 1),
     (521, 31, 32, 64, 24, 3, 2, 1, False, 1),      # ... three: stride 2
