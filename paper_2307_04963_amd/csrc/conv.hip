@@ -300,10 +300,15 @@ __global__ __launch_bounds__(64 * WM* WN) void conv_kernel(ConvP p) {
 // NS 1 is the memory-bound case of few K steps, whose speed follows the
 // number of workgroups in flight: its registers are capped for five waves
 // per SIMD (four with 128 x 128 and 128 x 256 tiles; one spilled register per
-// lane cost 20 %).
+// lane cost 20 %).  The others are capped for two waves per SIMD, or for one
+// where the LDS of four waves leaves room for one workgroup only.
+constexpr int lds_waves_per_simd(int bm, int bn, int waves, int ns) {
+  return ns == 1 ? (bn >= 128 ? 4 : 5) : waves == 4 && 2 * ns * (bm + bn) * 128 > 160 * 1024 ? 1 : 2;
+}
+
 template <int BM, int BN, int WM, int WN, int KS, int NS, bool LEAN, bool UNI>
-__global__ __launch_bounds__(64 * WM* WN) __attribute__((amdgpu_waves_per_eu(NS == 1 ? (BN >= 128 ? 4 : 5) : 2))) void conv_lds_kernel(
-    ConvP p) {
+__global__ __launch_bounds__(64 * WM* WN)
+    __attribute__((amdgpu_waves_per_eu(lds_waves_per_simd(BM, BN, WM * WN, NS)))) void conv_lds_kernel(ConvP p) {
   constexpr int NT = 64 * WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
