@@ -1535,11 +1535,11 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
   const bool listed = a.src_rows || a.src2_rows || a.res_rows || a.dst_rows;
   if (conv3_narrow(a, s)) return false;   // 16 / 32 channels: row lists allowed
   // 64 -> 64 channels on few pixels: the tile kernel, whose workgroups start
-  // without loading all weights first (us, register-weight kernel | tiles: 500
-  // images of 8x8 9.4 | 7.9, 20 of 56x56 12.5 | 9.7, 300 of 14x14 11.8 | 9.0, 64
-  // of 32x32 12.0 | 10.8; 735 tiles of 128 pixels and more: 15.0 | 15.2, 14.4 |
-  // 16.4)
-  if (vec_out && !listed && a.cin == 64 && a.cout == 64 && Mh <= 600 * 128 && conv3_tiles(a, s)) return false;
+  // without loading all weights first, while two per CU hold its 128 x 64 tiles
+  // (us, register-weight kernel | tiles: 500 images of 8x8 9.4 | 7.9, 300 of 14x14
+  // 11.8 | 9.0, 20 of 56x56 (490 tiles) 12.8 | 9.8, 22 of them (539) 12.5 | 13.7; 1078
+  // 18.9 | 23.0)
+  if (vec_out && !listed && a.cin == 64 && a.cout == 64 && Mh <= 512 * 128 && conv3_tiles(a, s)) return false;
   if (vec_out && (listed ? conv3_wres(a, s) : (conv3_wres(a, s) || conv3_tiles(a, s)))) return false;
   if (vec_out) {
     // deep K on few pixels per image: K ranges of one tile on several

@@ -25,17 +25,36 @@ CASES = [
     (5, 2, 65, 64, 64, 3, 1, 1, False, 1),       # 64 -> 64 channels on few pixels: 64 x 64 tiles
     (6, 56, 56, 64, 64, 3, 1, 1, True, 1),
     (257, 11, 11, 64, 64, 3, 1, 1, True, 2),     # 128 x 64 tiles
-    (600, 8, 16, 64, 64, 3, 1, 1, True, 1),      # the last tile count they take
-    (601, 8, 16, 64, 64, 3, 1, 1, True, 1),      # one more: the register-weight kernel
+    (512, 8, 16, 64, 64, 3, 1, 1, True, 1),      # the last tile count they take
+    (513, 8, 16, 64, 64, 3, 1, 1, True, 1),      # one more: the register-weight kernel
     (2, 5, 90, 64, 64, 3, 1, 1, False, 1),       # too wide for a patch: the register-weight kernel
     (5, 2, 65, 128, 64, 3, 1, 1, False, 1),      # two rows per image
     (4, 70, 2, 64, 128, 3, 1, 1, True, 1),       # two pixels per row
     (13, 7, 7, 256, 128, 3, 1, 1, True, 0),      # four input chunks
     (2, 3, 80, 64, 128, 3, 1, 1, False, 1),      # one pixel too wide: the implicit GEMM
     (300, 1, 1, 64, 128, 3, 1, 1, False, 1),     # 1 x 1 images: the implicit GEMM
+    (10, 56, 56, 64, 128, 3, 1, 1, True, 1),     # wide images, 64 input channels, 490 tiles of 128 x 64
+    (11, 56, 56, 64, 128, 3, 1, 1, True, 2),     # ... 539: the implicit GEMM
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "n{}_{}x{}_{}to{}".format(*c[:5]))
 def test_conv3_tiles(case):
     _case(*case, seed=hash(case) % (2 ** 31))
+
+
+@pytest.mark.parametrize("few,many,H,W,cout", [(20, 21, 56, 56, 64), (10, 11, 56, 56, 128), (3, 21, 37, 41, 512)])
+def test_rows_do_not_depend_on_the_batch(few, many, H, W, cout):
+    """64 input channels, on either side of the tile counts at which another
+    kernel takes the layer: the first images' outputs are the same bits."""
+    import numpy as np
+    import torch
+    from paper_2307_04963_amd import runtime
+    from workloads.configs import to_bf16_bits
+    rng = np.random.default_rng(many)
+    x = torch.from_numpy(rng.standard_normal((many, H, W, 64)).astype(np.float32)).bfloat16().cuda()
+    w = to_bf16_bits(rng.uniform(-0.1, 0.1, (cout, 3, 3, 64)).astype(np.float32))
+    packed = torch.from_numpy(runtime.pack_conv_weights(w).view(np.int16)).cuda()
+    a = runtime.conv(x, packed, cout, 3, 1, 1, act=2)[:few]
+    b = runtime.conv(x[:few].contiguous(), packed, cout, 3, 1, 1, act=2)
+    assert torch.equal(a.view(torch.int16), b.view(torch.int16))
