@@ -357,10 +357,22 @@ bool conv3_tiles(const ConvArgs& a, hipStream_t s) {
   if (a.k != 3 || a.stride != 1 || a.pad != 1 || a.src2 || a.out_f32 || a.Ho != a.H || a.Wo != a.W || a.cin % 64 ||
       a.cout % 64 || a.Kp != 9 * a.cin || a.src_rows || a.src2_rows || a.res_rows || a.dst_rows || a.pool || a.act > ACT_GELU)
     return false;
-  // images so small that the halo more than doubles the patch (4 x 4: 36
-  // pixels for 16) go to the implicit GEMM, whose K split fills the chip
+  // The smallest images (4 x 4, 3 x 3) go to the implicit GEMM and its K split:
+  // faster there up to ~120 of them and slower above (us, 512 -> 512 on 4 x 4, K
+  // split | these tiles: 60 images 17.5 | 23.7, 255 40 | 29, 1500 192 | 96).  The
+  // two sum in different orders, and a row's bits must not depend on how many
+  // rows come with it, so the shape alone decides.
   if (a.H * a.W <= 128 && 2 * a.H * a.W < (a.H + 2) * (a.W + 2)) return false;
-  if (a.W < 2 || patch_pixels(128, a.H, a.W) > 372) return false;   // (the widest images: 79 pixels)
+  const int cap = patch_pixels(128, a.H, a.W);
+  if (a.W < 2 || cap > 372) return false;   // (the widest images: 79 pixels)
+  const long Mh = static_cast<long>(a.nhint > 0 && a.nhint < a.n ? a.nhint : a.n) * a.H * a.W;
+  const long mt = (Mh + 127) / 128;
+  // 64 input channels on wide images (a patch over 244 pixels: 128 x 64 tiles, 72
+  // KB of weights streamed for each): with more tiles than two per CU hold, the
+  // implicit GEMM's 128 x 128 and 128 x 256 tiles (us, these | GEMM, 64 -> 256: 4
+  // images of 56x56, 392 tiles, 9.0 | 10.1; 8, 784, 19.4 | 17.8; 200, 289 | 204).  Its
+  // sums are in the same order.
+  if (a.cin == 64 && a.cout % 128 == 0 && cap > 244 && mt * (a.cout / 64) > 512) return false;
   Conv3TP p;
   p.src = a.src;
   p.w = a.w;
@@ -386,9 +398,6 @@ bool conv3_tiles(const ConvArgs& a, hipStream_t s) {
   // with fewer tiles than ~3 of every 4 CUs, the length of a tile's chain
   // counts and not its traffic.  Wide images (a patch over 244 pixels) and
   // other channel counts take 128 x 64.
-  const long Mh = static_cast<long>(a.nhint > 0 && a.nhint < a.n ? a.nhint : a.n) * a.H * a.W;
-  const long mt = (Mh + 127) / 128;
-  const int cap = patch_pixels(128, a.H, a.W);
   if (a.cout % 128 == 0 && cap <= 244 && mt * (a.cout / 128) >= 192) {
     p.nt = a.cout / 128;
     go3t<2, 2, 244, 3, 1, false>(p, a.act, s);
