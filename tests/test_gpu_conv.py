@@ -1,8 +1,9 @@
 """Sub-network convolution kernels through dycl_op_conv, element by element
 against the oracle's convolution (float64, bf16 inputs), at every geometry
 the launcher distinguishes: the halo-tiled kernel with register-resident
-weights (64 -> 64 channels, 3x3, stride 1: row tiles, partial row tiles,
-whole-image tiles with a ragged last tile, several tiles per workgroup), the
+weights (64 -> 64 channels, 3x3, stride 1, many pixels: row tiles, partial row
+tiles, whole-image tiles with a ragged last tile, several tiles per workgroup),
+the linear pixel tiles of the other 3x3 layers with 64-multiple channels, the
 direct-to-LDS implicit GEMM (1x1, 3x3, strided; with the K range of each
 tile split over workgroups for deep K on few pixels, and without), the
 RGB stem kernel (3-channel input read directly: 7x7 stride 2, ragged units
@@ -25,22 +26,29 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # n, H, W, cin, cout, k, stride, pad, residual, act
-    (3, 32, 32, 64, 64, 3, 1, 1, True, 1),      # row tiles (4 rows of 32)
-    (80, 32, 32, 64, 64, 3, 1, 1, True, 1),     # 640 tiles: several per workgroup
-    (5, 8, 8, 64, 64, 3, 1, 1, False, 1),       # two images per tile, ragged last tile
-    (1500, 8, 8, 64, 64, 3, 1, 1, True, 0),     # 750 image tiles
-    (3, 56, 56, 64, 64, 3, 1, 1, True, 1),      # 112-row tiles (2 rows of 56)
+    # 64 -> 64: the register-weight kernel above 512 tiles of 128 pixels (and on the smallest images)
+    (80, 32, 32, 64, 64, 3, 1, 1, True, 1),     # row tiles (4 rows of 32), 640 of them: several per workgroup
+    (1500, 8, 8, 64, 64, 3, 1, 1, True, 0),     # two images per tile, 750 of them
+    (1029, 8, 8, 64, 64, 3, 1, 1, False, 1),    # ... ragged last tile
+    (22, 56, 56, 64, 64, 3, 1, 1, True, 1),     # 112-pixel tiles (2 rows of 56)
     (9, 4, 4, 64, 64, 3, 1, 1, False, 2),       # eight images per tile, GELU
-    (40, 14, 14, 64, 64, 3, 1, 1, True, 1),     # 9-row tiles, 5-row remainder
-    (2, 9, 9, 64, 64, 3, 1, 1, False, 0),       # one 81-pixel image per tile
+    (341, 14, 14, 64, 64, 3, 1, 1, True, 1),    # 9-row tiles, 5-row remainder
+    (821, 9, 9, 64, 64, 3, 1, 1, False, 0),     # one 81-pixel image per tile
+    (1343, 7, 7, 64, 64, 3, 1, 1, True, 1),     # two 49-pixel images per tile
+    # ... and the linear pixel tiles below
+    (3, 32, 32, 64, 64, 3, 1, 1, True, 1),
+    (5, 8, 8, 64, 64, 3, 1, 1, False, 1),
+    (3, 56, 56, 64, 64, 3, 1, 1, True, 1),
+    (40, 14, 14, 64, 64, 3, 1, 1, True, 1),
+    (2, 9, 9, 64, 64, 3, 1, 1, False, 0),
     (3, 7, 7, 64, 64, 3, 1, 1, True, 1),
-    (4, 16, 16, 128, 128, 3, 1, 1, True, 1),    # halo tiles, streamed weights
-    (300, 16, 16, 128, 128, 3, 1, 1, True, 1),  # 600 units: several per workgroup
-    (9, 4, 4, 512, 512, 3, 1, 1, True, 1),      # 7 images per tile (patch capacity)
+    (4, 16, 16, 128, 128, 3, 1, 1, True, 1),    # linear pixel tiles of 64 x 64
+    (300, 16, 16, 128, 128, 3, 1, 1, True, 1),  # 600 tiles of 128 x 128
+    (9, 4, 4, 512, 512, 3, 1, 1, True, 1),      # K split on 4x4 images, two row tiles
     (3, 7, 7, 512, 512, 3, 1, 1, False, 0),
-    (2, 14, 14, 256, 256, 3, 1, 1, True, 1),    # 9-row tiles, 5-row remainder
+    (2, 14, 14, 256, 256, 3, 1, 1, True, 1),    # four input chunks, ragged last tile
     (2, 28, 28, 128, 128, 3, 1, 1, False, 2),
-    (5, 8, 8, 128, 64, 3, 1, 1, True, 1),       # 64-channel output tiles
+    (5, 8, 8, 128, 64, 3, 1, 1, True, 1),       # 64 x 64 tiles, one channel tile
     (40, 8, 8, 256, 256, 3, 1, 1, False, 1),
     (4, 16, 16, 64, 128, 3, 2, 1, False, 1),    # strided
     (4, 16, 16, 128, 256, 1, 1, 0, False, 0),   # 1x1
@@ -81,17 +89,17 @@ CASES = [
     (7, 9, 9, 64, 96, 3, 2, 1, True, 1),        # half-used second channel tile
     (3, 16, 16, 1024, 256, 1, 1, 0, True, 0),   # deep 1x1 with residual
     (2, 14, 14, 256, 512, 3, 2, 1, False, 2),   # strided, GELU
-    (2000, 8, 8, 128, 256, 3, 2, 1, False, 1),  # 128-pixel tiles, several units per workgroup
-    (2500, 8, 8, 128, 256, 3, 2, 1, True, 1),   # 256-pixel tiles, several units per workgroup
+    (2000, 8, 8, 128, 256, 3, 2, 1, False, 1),  # strided: 250 tiles of 128 x 256, three stages
+    (2500, 8, 8, 128, 256, 3, 2, 1, True, 1),   # 626 tiles of 128 x 128 on one stage
     (3, 6, 6, 600, 64, 1, 1, 0, False, 1),      # K = 600: the last step is partly padding
-    (24, 56, 56, 64, 256, 1, 1, 0, True, 1),    # one stage, 128 x 256 tiles (588 of them), residual
-    (24, 56, 56, 128, 256, 1, 1, 0, False, 2),  # one stage, 128 x 256 tiles, two K steps in turn, GELU
-    (48, 28, 28, 384, 512, 1, 1, 0, True, 1),   # one stage, 128 x 256 tiles, six K steps, residual
-    (40, 28, 28, 512, 128, 1, 1, 0, False, 1),  # one stage, 128 x 64 tiles, eight K steps
-    (42, 56, 56, 128, 128, 3, 2, 1, False, 1),  # strided 3x3, 516 tiles of 128 x 64: 64 x 128 tiles
-    (107, 14, 14, 1024, 256, 1, 1, 0, False, 1),  # 656 tiles: 64 x 128, rounds of two K steps
-    (107, 28, 28, 256, 256, 3, 2, 1, True, 1),    # strided 3x3 on 64 x 128 tiles, residual
-    (30, 14, 14, 1024, 256, 1, 1, 0, True, 2),    # 184 tiles: 64 x 64, GELU
+    (24, 56, 56, 64, 256, 1, 1, 0, True, 1),    # one stage, 128 x 128 tiles (1176 of them), residual
+    (24, 56, 56, 128, 256, 1, 1, 0, False, 2),  # ... two K steps in turn, GELU
+    (48, 28, 28, 384, 512, 1, 1, 0, True, 1),   # ... six K steps, residual
+    (40, 28, 28, 512, 128, 1, 1, 0, False, 1),  # 245 tiles of 128 x 128: three stages, eight K steps
+    (42, 56, 56, 128, 128, 3, 2, 1, False, 1),  # strided 3x3, 258 tiles of 128 x 128: two stages
+    (107, 14, 14, 1024, 256, 1, 1, 0, False, 1),  # 164 tiles of 128 x 256: three stages
+    (107, 28, 28, 256, 256, 3, 2, 1, True, 1),    # strided 3x3 on the same, residual
+    (30, 14, 14, 1024, 256, 1, 1, 0, True, 2),    # 184 tiles of 64 x 128, three stages, GELU
 ]
 
 

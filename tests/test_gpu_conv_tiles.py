@@ -16,15 +16,19 @@ CASES = [
     (201, 12, 12, 64, 128, 3, 1, 1, False, 1),   # 128 x 128 tiles: every tile crosses rows, most an image
     (31, 28, 29, 64, 128, 3, 1, 1, True, 1),     # odd width, ragged last tile
     (127, 14, 14, 128, 128, 3, 1, 1, True, 2),   # two input chunks, GELU
-    (100, 5, 5, 64, 1024, 3, 1, 1, False, 0),    # five images per tile, eight channel tiles
-    (9, 56, 56, 64, 128, 3, 1, 1, True, 1),      # 128 x 64 tiles: wide images
+    (125, 5, 5, 64, 1024, 3, 1, 1, False, 0),    # five images per tile, eight channel tiles
+    (61, 14, 14, 64, 512, 3, 1, 1, True, 1),     # four channel tiles, ragged last tile
+    (107, 14, 14, 256, 256, 3, 1, 1, True, 1),   # two channel tiles, four input chunks
+    (100, 5, 5, 64, 1024, 3, 1, 1, False, 0),    # 128 x 64 tiles: sixteen channel tiles
+    (9, 56, 56, 64, 128, 3, 1, 1, True, 1),      # wide images
     (3, 6, 79, 64, 128, 3, 1, 1, False, 1),      # the widest image a tile's patch holds
     (170, 14, 14, 128, 64, 3, 1, 1, False, 1),   # 64 output channels
     (1, 5, 5, 64, 128, 3, 1, 1, True, 1),        # 64 x 64 tiles: one tile, 25 of 64 pixels
     (3, 3, 43, 64, 128, 3, 1, 1, False, 1),
-    (5, 2, 65, 64, 64, 3, 1, 1, False, 1),       # 64 -> 64 channels on few pixels: 64 x 64 tiles
-    (6, 56, 56, 64, 64, 3, 1, 1, True, 1),
-    (257, 11, 11, 64, 64, 3, 1, 1, True, 2),     # 128 x 64 tiles
+    (5, 2, 65, 64, 64, 3, 1, 1, False, 1),       # 64 -> 64 channels on few pixels: 128 x 64 tiles
+    (6, 56, 56, 64, 64, 3, 1, 1, True, 1),       # 64 x 64 tiles
+    (257, 11, 11, 64, 64, 3, 1, 1, True, 2),     # 64 x 64 tiles, 243 of 128 x 64
+    (275, 11, 11, 64, 64, 3, 1, 1, True, 2),     # 128 x 64 tiles, 260
     (512, 8, 16, 64, 64, 3, 1, 1, True, 1),      # the last tile count they take
     (513, 8, 16, 64, 64, 3, 1, 1, True, 1),      # one more: the register-weight kernel
     (2, 5, 90, 64, 64, 3, 1, 1, False, 1),       # too wide for a patch: the register-weight kernel
