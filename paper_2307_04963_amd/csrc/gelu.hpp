@@ -10,12 +10,13 @@ namespace k {
 // 1 - t = (z / 2) t in [0, 1):  erfc(z) = t exp(-z^2) (erfcx(z) / t), and
 // log2(erfcx(z) / t) = u S(u) with S a polynomial of degree 7 (Chebyshev
 // interpolation on z <= 10, beyond which exp(-z^2) is below 1e-43).  One
-// reciprocal, one exponential and 9 fused multiply-adds, no branch; erff takes
-// both of its branches in every wave, several times that.  Against 64 bits
-// over |v| <= 12: largest error 3.8e-7 (4.5e-7 with 0.5 v (1 + erff)),
-// root mean square 6.5e-8 (7.4e-8), relative 1.7e-6 at worst (5e-2, where
-// 1 + erff cancels).  4096 x 1024 outputs of a 2048-long contraction: 29.4 ->
-// 24 us with the rest of the epilogue unchanged.
+// reciprocal, one exponential and 8 fused multiply-adds, no branch; erff takes
+// both of its branches in every wave, several times that.  Against 64 bits over
+// |v| <= 12, these operations rounded to 32 bits: largest error 3.8e-7, root mean
+// square 5.0e-8 (0.5 v (1 + erf), rounded alike: 4.5e-7 and 5.6e-8), relative 3e-6
+// for |v| <= 6, 5e-6 for 9 and 9e-6 for 12, from the rounding of an exponent of up
+// to 104 (that form: 5e-2 for 5, and no digit left at -6).  4096 x 1024 outputs of a 2048-long
+// contraction: 29.4 -> 26 us.
 __device__ __forceinline__ float gelu_f32(float v) {
   const float h = fminf(fabsf(v) * 0.35355339059327376f, 10.0f);   // z / 2
   const float t = __builtin_amdgcn_rcpf(1.0f + h);

@@ -757,14 +757,14 @@ void Spec::fuse_original_order_reads() {
 // outer tensors through the gate's list of executing rows, and the layer that
 // produces a scattered value writes it straight into the outer tensor's rows.
 // Only for bodies of convolutions that run on the implicit GEMM anyway (the
-// halo kernels stage contiguous images), whose gathered copies are read only
+// kernels with an input patch in LDS take contiguous images), whose gathered copies are read only
 // as main input or residual, and whose scattered values are each written by
 // one convolution that reads its target at most as its residual (an element
 // read and then written by the same thread).
 void Spec::fuse_gate_moves() {
   if (dt != DType::BF16) return;
-  // bodies on the streamed-weight halo kernel cannot take row lists; the
-  // register-weight one (64 -> 64 channels) can on whole-image tiles
+  // bodies on the linear pixel tiles cannot take row lists; the register-weight
+  // kernel (64 -> 64 channels) can on whole-image tiles
   auto halo_kind = [](const Node& nd, const TensorInfo& src) {
     const bool wres_images = nd.cin1 == 64 && nd.cout == 64 && src.H * src.W <= 128;
     return nd.k == 3 && nd.stride == 1 && nd.pad == 1 && nd.src2 < 0 && nd.cin1 % 64 == 0 && nd.cout % 64 == 0 &&
