@@ -123,16 +123,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
   const int NP = vidx(min(m0 + BM, M) - 1) - vf + 2 * PW + 3;
   // byte offset of each of this thread's patch slots; zero pixels get one that
   // no buffer reaches.  The buffer starts at the first pixel that the patch can
-  // hold (the one above and to the left of the tile's first), so the offsets
-  // span the patch and not the images that it lies in: those may be of any size.
-  const int mp = max(m0 - p.W - 1, 0);
+  // hold (pixel mq of the tile's first image: the one above and to the left of
+  // the tile's first), so the offsets span the patch and not the images that it
+  // lies in: those may be of any size.
+  const int img0 = quot(m0, p.dHW);
+  const int mq = max(m0 - img0 * HW - p.W - 1, 0), mp = img0 * HW + mq;
   uint32_t pofs[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int v = vf - PW - 1 + j * 32 + lrow;
     const int vr = quot(v, p.dPW), c = v - vr * PW, img = quot(vr, p.dH1), r = vr - img * (p.H + 1);
     pofs[j] = (c >= 1 && r >= 1 && img < n)
-                  ? static_cast<uint32_t>((img * HW + (r - 1) * p.W + (c - 1) - mp) * cin * 2 + lch * 16)
+                  ? static_cast<uint32_t>(((img - img0) * HW + (r - 1) * p.W + (c - 1) - mq) * cin * 2 + lch * 16)
                   : 0xC0000000u;
   }
   const uint16_t* const sbase = p.src + static_cast<size_t>(mp) * cin;
@@ -368,11 +370,11 @@ bool conv3_tiles(const ConvArgs& a, hipStream_t s) {
   const long Mh = static_cast<long>(a.nhint > 0 && a.nhint < a.n ? a.nhint : a.n) * a.H * a.W;
   const long mt = (Mh + 127) / 128;
   // 64 input channels on wide images (a patch over 244 pixels: 128 x 64 tiles, 72
-  // KB of weights streamed for each): with more tiles than two per CU hold, the
-  // implicit GEMM's 128 x 128 and 128 x 256 tiles (us, these | GEMM, 64 -> 256: 4
-  // images of 56x56, 392 tiles, 9.0 | 10.1; 8, 784, 19.4 | 17.8; 200, 289 | 204).  Its
-  // sums are in the same order.
-  if (a.cin == 64 && a.cout % 128 == 0 && cap > 244 && mt * (a.cout / 64) > 512) return false;
+  // KB of weights streamed for each): with many tiles, the implicit GEMM's 128 x 128
+  // and 128 x 256 ones (us, these | GEMM, 64 -> 256: 4 images of 56x56, 392 tiles,
+  // 9.0 | 10.1; 6, 588, 16.7 | 17.6; 8, 784, 19.4 | 17.8; 200, 289 | 204).  Its sums are
+  // in the same order.
+  if (a.cin == 64 && a.cout % 128 == 0 && cap > 244 && mt * (a.cout / 64) > 640) return false;
   Conv3TP p;
   p.src = a.src;
   p.w = a.w;
