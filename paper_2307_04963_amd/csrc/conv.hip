@@ -1590,7 +1590,10 @@ bool conv_bf16(const ConvArgs& a, hipStream_t s) {
         finish(ksplit_finish_kernel<ACT_NONE>);
       return false;
     }
-    if (a.gap_part && !a.out_f32 && !a.dst_rows && a.act != ACT_LSTM && a.Ho * a.Wo >= 32) p.gap = a.gap_part;
+    // (a layer that runs on the linear pixel tiles at other row counts leaves the
+    // pooling to the exit as there: a row's sums keep one order)
+    if (a.gap_part && !a.out_f32 && !a.dst_rows && a.act != ACT_LSTM && a.Ho * a.Wo >= 32 && !conv3_tiles_shape(a))
+      p.gap = a.gap_part;
     dispatch_lds(a.k, c, p, s, 1, uni);
     return p.gap != nullptr;
   }

@@ -355,7 +355,7 @@ void go3t(const Conv3TP& p, int act, hipStream_t s) {
 
 }  // namespace
 
-bool conv3_tiles(const ConvArgs& a, hipStream_t s) {
+bool conv3_tiles_shape(const ConvArgs& a) {
   if (a.k != 3 || a.stride != 1 || a.pad != 1 || a.src2 || a.out_f32 || a.Ho != a.H || a.Wo != a.W || a.cin % 64 ||
       a.cout % 64 || a.Kp != 9 * a.cin || a.src_rows || a.src2_rows || a.res_rows || a.dst_rows || a.pool || a.act > ACT_GELU)
     return false;
@@ -365,15 +365,19 @@ bool conv3_tiles(const ConvArgs& a, hipStream_t s) {
   // two sum in different orders, and a row's bits must not depend on how many
   // rows come with it, so the shape alone decides.
   if (a.H * a.W <= 128 && 2 * a.H * a.W < (a.H + 2) * (a.W + 2)) return false;
+  return a.W >= 2 && patch_pixels(128, a.H, a.W) <= 372;   // (the widest images: 79 pixels)
+}
+
+bool conv3_tiles(const ConvArgs& a, hipStream_t s) {
+  if (!conv3_tiles_shape(a)) return false;
   const int cap = patch_pixels(128, a.H, a.W);
-  if (a.W < 2 || cap > 372) return false;   // (the widest images: 79 pixels)
   const long Mh = static_cast<long>(a.nhint > 0 && a.nhint < a.n ? a.nhint : a.n) * a.H * a.W;
   const long mt = (Mh + 127) / 128;
   // 64 input channels on wide images (a patch over 244 pixels: 128 x 64 tiles, 72
   // KB of weights streamed for each): with many tiles, the implicit GEMM's 128 x 128
   // and 128 x 256 ones (us, these | GEMM, 64 -> 256: 4 images of 56x56, 392 tiles,
   // 9.0 | 10.1; 6, 588, 16.7 | 17.6; 8, 784, 19.4 | 17.8; 200, 289 | 204).  Its sums are
-  // in the same order.
+  // in the same order.  (Pooling sums are not: see the caller.)
   if (a.cin == 64 && a.cout % 128 == 0 && cap > 244 && mt * (a.cout / 64) > 640) return false;
   Conv3TP p;
   p.src = a.src;

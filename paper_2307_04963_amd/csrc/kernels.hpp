@@ -168,6 +168,9 @@ bool conv3_narrow(const ConvArgs& a, hipStream_t s);
 // linear pixel tiles.  Returns false (launching nothing) for other arguments.
 bool conv3_tiles(const ConvArgs& a, hipStream_t s);
 
+// The part of conv3_tiles' rule that does not look at the number of rows.
+bool conv3_tiles_shape(const ConvArgs& a);
+
 // K ranges per output tile for the layer shape (1: none).  A split layer
 // needs conv_ksplit_bytes of workspace; without it the layer runs unsplit
 // (the same sums in another order).  Depends on the shape only, so every

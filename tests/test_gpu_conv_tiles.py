@@ -62,3 +62,46 @@ def test_rows_do_not_depend_on_the_batch(few, many, H, W, cout):
     a = runtime.conv(x, packed, cout, 3, 1, 1, act=2)[:few]
     b = runtime.conv(x[:few].contiguous(), packed, cout, 3, 1, 1, act=2)
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("mode", ["sync", "device"])
+def test_exit_after_a_wide_layer_does_not_depend_on_the_batch(mode):
+    """An exit pools what a wide layer of 64 input channels wrote, on either
+    side of the tile count at which another kernel takes the layer: the first
+    images' logits are the same bits.  (600 classes: the exit's pooling is a
+    launch of its own, or the layer's.)"""
+    import json
+    import numpy as np
+    import torch
+    from paper_2307_04963_amd import runtime
+    from workloads.configs import to_bf16_bits
+    rng = np.random.default_rng(3)
+    blob = bytearray()
+
+    def add(arr, bf16=False):
+        blob.extend(b"\0" * ((-len(blob)) % 256))
+        at = len(blob)
+        arr = np.asarray(arr, np.float32)
+        blob.extend((to_bf16_bits(arr) if bf16 else arr).tobytes())
+        return at
+
+    spec = {"version": 1, "dtype": "bf16", "input": {"name": "x", "shape": [56, 56, 64]}, "n_out": 600,
+            "nodes": [{"op": "conv", "src": "x", "dst": "y", "k": 3, "stride": 1, "pad": 1, "cout": 128, "act": "relu",
+                       "w": {"off": add(rng.uniform(-0.1, 0.1, (128, 3, 3, 64)), True)}, "scale": add(np.ones(128)),
+                       "shift": add(np.zeros(128))},
+                      {"op": "exit", "src": "y", "w": add(rng.uniform(-1, 1, (600, 128))), "b": add(np.zeros(600)),
+                       "ncls": 600, "index": 0, "final": True}]}
+    plan = runtime.Plan(json.dumps(spec), bytes(blob), 14)
+    plan.set_host_mode(mode)
+    x = torch.from_numpy(rng.standard_normal((14, 56, 56, 64)).astype(np.float32)).bfloat16().cuda()
+
+    def run(n):
+        logits, rec, _ = plan.outputs(n)
+        plan.run(x[:n].contiguous(), None, logits, rec)
+        torch.cuda.synchronize()
+        return logits.clone()
+
+    many = run(14)
+    for n in (1, 13):
+        assert torch.equal(run(n), many[:n])
+    plan.close()
